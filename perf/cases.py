@@ -78,7 +78,7 @@ def draw(rng):
         elif rng.random() < 0.3:
             case["mixed"] = round(rng.uniform(0.05, 0.5), 2)
         if rng.random() < 0.3:
-            case["ragged"] = True
+            case["ragged"], case["batches"] = True, min(r, 250)
         return case
     if op == "submit":
         b = _log(rng, 4096, 1 << 17)
