@@ -7,7 +7,8 @@
 //   k_sort_hist / k_sort_pass : stable LSD radix sort of one batch (the
 //       "sort the batch" step of sec. III-B / Fig. 2(a)): one histogram
 //       kernel, then one counting pass per 8-bit digit with decoupled
-//       look-back.  The batch is read back to front, so among equal key
+//       look-back (k_lsd_up / k_lsd_scan / k_lsd_down: a pass over more than
+//       256 tiles, with none).  The batch is read back to front, so among equal key
 //       variables the later batch position comes first (the last duplicate
 //       wins), and padded with copies of its last element (sec. IV-A).
 //   k_msd_scatter / k_local_sort : the same stable order for batches of at
@@ -623,6 +624,270 @@ __global__ __launch_bounds__(kThreads) void k_sort_pass(SortArgs a, int pass) {
                  (pass == a.passes - 1) ? a.out_fence : nullptr, false, &m.err[1], L);
 }
 
+// ------------------------------------------------------------ large digit passes
+// Stable ranking of one item per lane by digit d among the valid lanes of
+// the wave: returns the item's position after the entries already counted
+// in wcnt[d], and adds the wave's count of d to wcnt[d].
+template <int kBits>
+__device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool valid, uint32_t* wcnt) {
+  const uint64_t on = ballot(valid);
+  uint32_t lo = static_cast<uint32_t>(on), hi = static_cast<uint32_t>(on >> 32);
+#pragma unroll
+  for (int bit = 0; bit < kBits; ++bit) {
+    // x is all ones where the lane's bit is set: the lanes that agree with
+    // it are ~(m ^ x), one three-input logic operation a half.
+    const uint32_t x = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(d), bit, 1));
+    const uint64_t m = ballot(x != 0u);
+    lo &= ~(static_cast<uint32_t>(m) ^ x);
+    hi &= ~(static_cast<uint32_t>(m >> 32) ^ x);
+  }
+  const uint64_t peers = (static_cast<uint64_t>(hi) << 32) | lo;
+  const uint32_t r = count_below(peers);
+  uint32_t prev = 0;
+  if (valid) prev = wcnt[d];
+  if (valid && r == 0) wcnt[d] = prev + static_cast<uint32_t>(__popcll(peers));
+  return prev + r;
+}
+
+// The digit passes of a sort of more than kMsdMaxTiles tiles.  Such a pass is
+// bound by memory, and a decoupled look-back keeps it from it: every tile's
+// 256 counts travel between the 8 XCDs through memory, some microseconds a
+// hop, with hundreds of tiles waiting.  Here a fixed set of work-groups
+// each owns one contiguous chunk of the input for the whole pass: k_lsd_up
+// counts the digits of every chunk, k_lsd_scan turns the counts into each
+// chunk's first output position per digit (a work-group per digit), and
+// k_lsd_down walks its chunk tile by tile with running positions.  No
+// work-group waits for another, for 4 B per element read once more.
+// A pass over 2^25 pairs takes 216 us in all (about 400 with the look-back
+// over tiles of 2048), of which reading and writing alone take 124, the
+// ranking 59 and the scattered writes 42.  Tiles of 8192: a digit's run in a
+// tile is then 32 elements, one 128-byte line; tiles of 4096 took 257 us (256
+// threads) and of 16384 240 us (one work-group a CU).
+constexpr int kLsdThreads = 512;
+constexpr int kLsdWaves = kLsdThreads / 64;
+constexpr int kLsdItems = 16;
+constexpr uint32_t kLsdTile = kLsdThreads * kLsdItems;
+constexpr uint32_t kLsdMaxGroups = 512;  // two work-groups on each of 256 CUs
+
+// Work-groups of a pass over b elements and the tiles that each takes.
+struct LsdGrid {
+  uint32_t groups, tiles_per_group;
+};
+inline LsdGrid lsd_grid(uint32_t b) {
+  const uint32_t tiles = static_cast<uint32_t>((static_cast<uint64_t>(b) + kLsdTile - 1) / kLsdTile);
+  const uint32_t per = (tiles + kLsdMaxGroups - 1) / kLsdMaxGroups;
+  return {(tiles + per - 1) / per, per};
+}
+
+// Input of a pass: the previous pass's output, or nulls for the caller's batch.
+struct LsdSrc {
+  const uint32_t* kv;
+  const uint32_t* val;
+};
+
+// Where element e < b of the batch, as the sort sees it (read back to front and
+// padded in front), stands in the caller's arrays.
+__device__ __forceinline__ uint32_t src_index(const BatchSrc& s, uint32_t e) {
+  const uint32_t x = s.b - 1 - e;
+  return x < s.n - 1 ? x : s.n - 1;
+}
+__device__ __forceinline__ uint32_t src_kv(const BatchSrc& s, uint32_t raw, uint32_t i) {
+  if (s.mode == kEncoded) return raw;
+  const uint32_t st = s.mode == kMixed ? (s.is_delete[i] ? 0u : 1u) : (s.mode == kDelete ? 0u : 1u);
+  return (raw << 1) | st;
+}
+
+__global__ __launch_bounds__(kLsdThreads) void k_lsd_up(SortArgs a, LsdSrc in, int shift,
+                                                        uint32_t tiles_per_group,
+                                                        uint32_t* counts) {
+  __shared__ uint32_t h[kLsdWaves][kRadix];
+  const uint32_t tid = threadIdx.x, wave = tid >> 6;
+  const uint32_t b = a.src.b;
+  for (uint32_t i = tid; i < kLsdWaves * kRadix; i += kLsdThreads) (&h[0][0])[i] = 0u;
+  __syncthreads();
+  const uint64_t lo = static_cast<uint64_t>(blockIdx.x) * tiles_per_group * kLsdTile;
+  const uint64_t hi64 = lo + static_cast<uint64_t>(tiles_per_group) * kLsdTile;
+  const uint32_t hi = hi64 < b ? static_cast<uint32_t>(hi64) : b;
+  constexpr int kU = 8;  // loads in flight per thread
+  for (uint64_t base = lo; base < hi; base += static_cast<uint64_t>(kLsdThreads) * kU) {
+    uint32_t x[kU], idx[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint64_t e = base + static_cast<uint64_t>(u) * kLsdThreads + tid;
+      const uint32_t ec = e < hi ? static_cast<uint32_t>(e) : hi - 1;
+      idx[u] = in.kv == nullptr ? src_index(a.src, ec) : ec;
+      x[u] = in.kv == nullptr ? a.src.keys[idx[u]] : in.kv[idx[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint64_t e = base + static_cast<uint64_t>(u) * kLsdThreads + tid;
+      const uint32_t kv = in.kv == nullptr ? src_kv(a.src, x[u], idx[u]) : x[u];
+      if (e < hi) atomicAdd(&h[wave][(kv >> shift) & (kRadix - 1)], 1u);
+    }
+  }
+  __syncthreads();
+  if (tid < kRadix) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int w = 0; w < kLsdWaves; ++w) c += h[w][tid];
+    counts[static_cast<size_t>(tid) * gridDim.x + blockIdx.x] = c;
+  }
+}
+
+// Work-group d: the exclusive scan of digit d's counts over the chunks (at
+// most 2 kThreads of them), in place; the digit's total goes to totals[d].
+static_assert(kLsdMaxGroups <= 2 * kThreads, "two counts per thread");
+__global__ __launch_bounds__(kThreads) void k_lsd_scan(uint32_t* counts, uint32_t groups,
+                                                       uint32_t* totals) {
+  __shared__ uint32_t tmp[kWaves];
+  uint32_t* row = counts + static_cast<size_t>(blockIdx.x) * groups;
+  const uint32_t i = 2 * threadIdx.x;
+  const uint32_t c0 = i < groups ? row[i] : 0u, c1 = i + 1 < groups ? row[i + 1] : 0u;
+  const uint32_t ex = block_excl_scan(c0 + c1, tmp);
+  if (i < groups) row[i] = ex;
+  if (i + 1 < groups) row[i + 1] = ex + c0;
+  if (threadIdx.x == kThreads - 1) totals[blockIdx.x] = ex + c0 + c1;
+}
+
+struct LsdLds {
+  uint32_t kv[kLsdTile];
+  uint32_t val[kLsdTile];
+  uint32_t wcnt[kLsdWaves][kRadix];
+  uint32_t run[kRadix];  // the tile's first output position of each digit, minus its first in LDS
+  uint32_t tmp[kLsdWaves];
+};
+
+// kFirst: pass 0, which reads the caller's batch.
+template <bool kFirst>
+__global__ __launch_bounds__(kLsdThreads, 4) void k_lsd_down(SortArgs a, LsdSrc in, int shift,
+                                                          uint32_t tiles_per_group,
+                                                          const uint32_t* counts,
+                                                          const uint32_t* totals, uint32_t* o_kv,
+                                                          uint32_t* o_val, uint32_t* o_fence) {
+  __shared__ LsdLds L;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t b = a.src.b;
+  // Work-group-wide exclusive scan of one value per digit thread.
+  auto scan = [&](uint32_t x) {
+    const uint32_t inc = wave_incl_scan(x, lane);
+    if (lane == 63) L.tmp[wave] = inc;
+    __syncthreads();
+    uint32_t pre = 0;
+    for (uint32_t w = 0; w < wave; ++w) pre += L.tmp[w];
+    __syncthreads();
+    return pre + inc - x;
+  };
+  const uint32_t tot = tid < kRadix ? totals[tid] : 0u;
+  const uint32_t first = scan(tot);
+  uint32_t pos = 0;  // digit thread: next output position of digit tid
+  if (tid < kRadix) pos = first + counts[static_cast<size_t>(tid) * gridDim.x + blockIdx.x];
+
+  // Item i of lane l of wave w is tile element w * 64 * I + 64 i + l.  A whole
+  // tile (and, in pass 0, one without padding) is read from a uniform base
+  // with constant offsets between a thread's items; others clamp each index.
+  const uint32_t at0 = wave * 64 * kLsdItems + lane;
+  const uint32_t* vp = a.src.vals != nullptr ? a.src.vals : a.src.keys;
+  uint32_t kv[kLsdItems], val[kLsdItems];
+  auto load_tile = [&](uint32_t tb) {
+    const bool whole = b - tb >= kLsdTile;
+    if (kFirst && whole && tb >= b - a.src.n && a.src.mode != kMixed) {
+      const uint32_t x0 = b - tb - kLsdTile, y = kLsdTile - 1 - at0;
+      const uint32_t* pk = a.src.keys + x0;
+      const uint32_t* pv = vp + x0;
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i) kv[i] = pk[y - i * 64];
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i) val[i] = pv[y - i * 64];
+    } else if (!kFirst && whole) {
+      const uint32_t* pk = in.kv + tb;
+      const uint32_t* pv = in.val + tb;
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i) kv[i] = pk[at0 + i * 64];
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i) val[i] = pv[at0 + i * 64];
+    } else {
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i) {
+        const uint32_t e = tb + at0 + i * 64, ec = e < b ? e : b - 1;
+        const uint32_t x = kFirst ? src_index(a.src, ec) : ec;
+        kv[i] = kFirst ? a.src.keys[x] : in.kv[x];
+        val[i] = kFirst ? vp[x] : in.val[x];
+        if (kFirst && a.src.mode == kMixed) {
+          kv[i] = src_kv(a.src, kv[i], x);
+          if ((kv[i] & 1u) == 0u) val[i] = 0u;
+        }
+      }
+    }
+    if (kFirst && a.src.mode != kMixed && a.src.mode != kEncoded) {
+      const uint32_t st = a.src.mode == kDelete ? 0u : 1u;
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i) {
+        kv[i] = (kv[i] << 1) | st;
+        val[i] = st ? val[i] : 0u;  // tombstones carry value 0
+      }
+    }
+  };
+  const uint32_t t0 = blockIdx.x * tiles_per_group;
+  const uint32_t tiles = static_cast<uint32_t>((static_cast<uint64_t>(b) + kLsdTile - 1) / kLsdTile);
+  const uint32_t t1 = t0 + tiles_per_group < tiles ? t0 + tiles_per_group : tiles;
+  for (uint32_t t = t0; t < t1; ++t) {
+    const uint32_t tb = t * kLsdTile;
+    const uint32_t n = (b - tb) < kLsdTile ? (b - tb) : kLsdTile;
+    load_tile(tb);
+    for (uint32_t i = lane; i < kRadix; i += 64) L.wcnt[wave][i] = 0u;  // this wave's own
+    uint32_t off[kLsdItems];
+    if (n == kLsdTile) {
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i)
+        off[i] = wave_rank<kRadixBits>((kv[i] >> shift) & (kRadix - 1), true, L.wcnt[wave]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kLsdItems; ++i)
+        off[i] = wave_rank<kRadixBits>((kv[i] >> shift) & (kRadix - 1), at0 + i * 64 < n,
+                                       L.wcnt[wave]);
+    }
+    __syncthreads();
+    uint32_t c = 0;
+    if (tid < kRadix) {
+#pragma unroll
+      for (int w = 0; w < kLsdWaves; ++w) {
+        const uint32_t x = L.wcnt[w][tid];
+        L.wcnt[w][tid] = c;
+        c += x;
+      }
+    }
+    const uint32_t loc = scan(c);
+    if (tid < kRadix) {
+#pragma unroll
+      for (int w = 0; w < kLsdWaves; ++w) L.wcnt[w][tid] += loc;
+      L.run[tid] = pos - loc;
+      pos += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kLsdItems; ++i) {
+      if (at0 + i * 64 < n) {
+        const uint32_t at = L.wcnt[wave][(kv[i] >> shift) & (kRadix - 1)] + off[i];
+        L.kv[at] = kv[i];
+        L.val[at] = val[i];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kLsdItems; ++i) {
+      const uint32_t x = static_cast<uint32_t>(i) * kLsdThreads + tid;
+      if (x < n) {
+        const uint32_t k = L.kv[x];
+        const uint32_t o = L.run[(k >> shift) & (kRadix - 1)] + x;
+        o_kv[o] = k;
+        o_val[o] = L.val[x];
+        put_fence(o_fence, b, o, k);
+      }
+    }
+    __syncthreads();
+  }
+}
+
 // ------------------------------------------------------------ MSD sort
 // For batches of at most kMsdMaxTiles tiles the sort exchanges data across
 // the device only once: each tile grouped in place by its top kTopBits-bit
@@ -631,25 +896,6 @@ __global__ __launch_bounds__(kThreads) void k_sort_pass(SortArgs a, int pass) {
 // its own by one work-group on the remaining bits (in LDS when it fits,
 // streaming through the bucket's global range otherwise).  Two kernels
 // instead of 1 + passes, and no look-back chains.
-
-// Stable ranking of one item per lane by digit d among the valid lanes of
-// the wave: returns the item's position after the entries already counted
-// in wcnt[d], and adds the wave's count of d to wcnt[d].
-template <int kBits>
-__device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool valid, uint32_t* wcnt) {
-  uint64_t peers = ballot(valid);
-#pragma unroll
-  for (int bit = 0; bit < kBits; ++bit) {
-    const bool set = (d >> bit) & 1u;
-    const uint64_t m = ballot(set);
-    peers &= set ? m : ~m;
-  }
-  const uint32_t r = count_below(peers);
-  uint32_t prev = 0;
-  if (valid) prev = wcnt[d];
-  if (valid && r == 0) wcnt[d] = prev + static_cast<uint32_t>(__popcll(peers));
-  return prev + r;
-}
 
 // Stable ranks of a wave's items among equal top digits, item i of every
 // lane after item i - 1 (tile order is item-major within the wave).  The
@@ -2450,7 +2696,7 @@ inline unsigned grid_for(uint64_t n, uint64_t per) { return static_cast<unsigned
 template <typename Kernel, typename... Args>
 hipError_t launch(Kernel k, unsigned grid, unsigned block, hipStream_t s, const KTimer* t,
                   Args... args) {
-  if (t != nullptr && t->start != nullptr)
+  if (t != nullptr && (t->start != nullptr || t->stop != nullptr))
     hipExtLaunchKernelGGL(k, dim3(grid), dim3(block), 0, s, t->start, t->stop, 0, args...);
   else
     k<<<grid, block, 0, s>>>(args...);
@@ -2598,6 +2844,39 @@ hipError_t launch_sort(const SortArgs& a, hipStream_t stream, const KTimer* time
     e = launch_buckets(a, stream, timers ? &timers[1] : nullptr);
     if (e == hipSuccess) *launched = 2;
     return e;
+  }
+  if (tiles > static_cast<uint32_t>(kMsdMaxTiles)) {
+    // Counts and totals live in the look-back words' region, which this path
+    // does not use otherwise: at least 4 x 257 x 256 words.
+    static_assert(static_cast<uint64_t>(kMaxPasses) * (kMsdMaxTiles + 1) * kRadix >=
+                      static_cast<uint64_t>(kRadix) * kLsdMaxGroups + kRadix,
+                  "digit counts fit the look-back region");
+    const LsdGrid g = lsd_grid(a.src.b);
+    uint32_t* counts = a.meta.status;
+    uint32_t* totals = counts + static_cast<size_t>(kRadix) * g.groups;
+    for (int p = 0; p < a.passes; ++p) {
+      const LsdSrc in = p == 0 ? LsdSrc{nullptr, nullptr}
+                               : LsdSrc{a.tmp_kv[(p - 1) & 1], a.tmp_val[(p - 1) & 1]};
+      const bool last = p == a.passes - 1;
+      const int shift = a.lo_bit + kRadixBits * p;
+      // A pass is timed from its count to its scatter; the first kernel of
+      // all has the histogram's timer to itself.
+      const KTimer begin{timers != nullptr && p > 0 ? timers[1 + p].start : nullptr, nullptr};
+      const KTimer end{timers != nullptr && p == 0 ? timers[1].start : nullptr,
+                       timers != nullptr ? timers[1 + p].stop : nullptr};
+      hipError_t e = launch(k_lsd_up, g.groups, kLsdThreads, stream,
+                            timers != nullptr && p == 0 ? &timers[0] : &begin, a, in, shift,
+                            g.tiles_per_group, counts);
+      if (e != hipSuccess) return e;
+      e = launch(k_lsd_scan, kRadix, kThreads, stream, nullptr, counts, g.groups, totals);
+      if (e != hipSuccess) return e;
+      e = launch(p == 0 ? k_lsd_down<true> : k_lsd_down<false>, g.groups, kLsdThreads, stream, &end, a, in, shift, g.tiles_per_group,
+                 counts, totals, last ? a.out_kv : a.tmp_kv[p & 1],
+                 last ? a.out_val : a.tmp_val[p & 1], last ? a.out_fence : nullptr);
+      if (e != hipSuccess) return e;
+    }
+    *launched = 1 + a.passes;
+    return hipSuccess;
   }
   const uint32_t hist_grid = tiles < static_cast<uint32_t>(kMaxHistBlocks) ? tiles : kMaxHistBlocks;
   hipError_t e = launch(k_sort_hist, hist_grid, kThreads, stream, timers ? &timers[0] : nullptr, a);
