@@ -302,10 +302,10 @@ LSM_API lsm_status_t lsm_range(lsm_t h, const uint32_t* d_lo, const uint32_t* d_
  * batches are sorted together, then merged with the old levels it takes
  * over.  From an empty dictionary this is a sort per level and no merge.
  *   d_keys, d_vals : n keys and values (device), read only.
- * n == 0 is a no-op.  Allocates scratch for the call (the sort's ping-pong
- * and look-back words for the largest level built, two merge buffers when
- * old levels are taken over) and frees it before returning; synchronises
- * the stream.  LSM_EINVAL, LSM_EKEY (checked mode; nothing changed),
+ * n == 0 is a no-op.  Needs scratch (the sort's ping-pong and counts for the
+ * largest level built, two merge buffers when old levels are taken over),
+ * which the handle keeps for later calls and shares with lsm_cleanup;
+ * synchronises the stream.  LSM_EINVAL, LSM_EKEY (checked mode; nothing changed),
  * LSM_ENOMEM (nothing changed), LSM_ECAPACITY (n >= 2^32 or a level above
  * 2^31 elements), LSM_EHIP.
  */
@@ -340,8 +340,9 @@ LSM_API lsm_status_t lsm_predecessor(lsm_t h, const uint32_t* d_q, uint32_t nq,
  * smaller levels.  Every query answer is unchanged; later batches insert on
  * top of r' as usual.
  *   h_valid : HOST pointer (may be NULL); receives the number of valid pairs.
- * Allocates scratch of up to 2 r b (key, value) pairs for the call and frees
- * it before returning; synchronises the stream.  LSM_EINVAL, LSM_ENOMEM
+ * Needs scratch of up to 2 r b (key, value) pairs, which the handle keeps for
+ * later calls and shares with lsm_bulk_insert (it gives it back when another
+ * of its allocations finds no memory); synchronises the stream.  LSM_EINVAL, LSM_ENOMEM
  * (nothing changed), LSM_ECAPACITY (r b >= 2^32), LSM_EHIP.
  */
 LSM_API lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid);
@@ -418,8 +419,9 @@ LSM_API uint64_t lsm_num_batches(lsm_t h);
 
 /*
  * Allocation-failure injection, for tests of the strong guarantee: the next
- * n device allocations of the handle succeed and every later one fails as if
- * the device were out of memory (the call then returns LSM_ENOMEM and leaves
+ * n device allocations of the handle (each part of the scratch that it keeps
+ * for bulk insertion and cleanup counts as one in every call) succeed and
+ * every later one fails as if the device were out of memory (the call then returns LSM_ENOMEM and leaves
  * the dictionary as it was).  A negative n turns the injection off.
  */
 LSM_API lsm_status_t lsm_fail_alloc_after(lsm_t h, int64_t n);

@@ -113,6 +113,15 @@ struct lsm_s {
   // when its address could not be looked up.
   FixedScratch fixed = {nullptr, nullptr};
 
+  // Scratch of lsm_bulk_insert and lsm_cleanup, grown to the largest such call
+  // and kept for the next one: allocating and freeing it took 1 to 13 ms a
+  // call (hipFree waits for the device and hands the memory back to the
+  // driver), more than the kernels of either call on 2^24 pairs.  Given back
+  // when another allocation of the handle finds no memory.
+  void* work = nullptr;
+  size_t work_bytes = 0;
+  bool work_busy = false;
+
   uint64_t* h_pinned = nullptr;  // read-backs (range total, key check)
   // Largest top-digit bucket of the most recent sort, written by the sort
   // kernels into mapped host memory and read without synchronising (a
@@ -177,12 +186,29 @@ struct DeviceGuard {
   }
 };
 
-lsm_status_t dev_alloc(lsm_t h, void** p, size_t bytes) {
-  *p = nullptr;
-  if (h->fail_after == 0) return LSM_ENOMEM;
+// One allocation as the failure injection counts them: false when it fails.
+bool alloc_allowed(lsm_t h) {
+  if (h->fail_after == 0) return false;
   if (h->fail_after > 0) --h->fail_after;
+  return true;
+}
+
+lsm_status_t dev_alloc(lsm_t h, void** p, size_t bytes, bool counted = true) {
+  *p = nullptr;
+  if (counted && !alloc_allowed(h)) return LSM_ENOMEM;
   if (bytes == 0) bytes = 4;
-  if (hipMalloc(p, bytes) != hipSuccess) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && h->work != nullptr && !h->work_busy) {
+    // The kept scratch makes room (both calls that use it end with a
+    // synchronisation, so no work on the device still needs it).
+    (void)hipGetLastError();
+    (void)hipFree(h->work);
+    h->device_bytes -= h->work_bytes;
+    h->work = nullptr;
+    h->work_bytes = 0;
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
     return LSM_ENOMEM;
@@ -197,6 +223,45 @@ void dev_free(lsm_t h, void* p, size_t bytes) {
     h->device_bytes -= bytes;
   }
 }
+
+// The kept scratch, cut into 256-byte aligned parts for one call: add() every
+// part, claim() once (it allocates only when the scratch has to grow), then
+// part() gives the addresses.  Free for the next call when the object goes.
+struct WorkArea {
+  lsm_t h;
+  size_t at[10] = {};
+  size_t total = 0;
+  int n = 0;
+  bool claimed = false;
+  explicit WorkArea(lsm_t handle) : h(handle) {}
+  ~WorkArea() {
+    if (claimed) h->work_busy = false;
+  }
+  int add(size_t bytes) {
+    at[n] = total;
+    total += (bytes + 255) & ~static_cast<size_t>(255);
+    return n++;
+  }
+  // Every part counts as an allocation for the failure injection, whether or
+  // not the scratch has to grow.
+  lsm_status_t claim() {
+    for (int i = 0; i < n; ++i)
+      if (!alloc_allowed(h)) return LSM_ENOMEM;
+    if (h->work_bytes < total) {
+      dev_free(h, h->work, h->work_bytes);
+      h->work = nullptr;
+      h->work_bytes = 0;
+      const lsm_status_t s = dev_alloc(h, &h->work, total, false);
+      if (s != LSM_OK) return s;
+      h->work_bytes = total;
+    }
+    h->work_busy = claimed = true;
+    return LSM_OK;
+  }
+  uint32_t* part(int i) const {
+    return reinterpret_cast<uint32_t*>(static_cast<char*>(h->work) + at[i]);
+  }
+};
 
 inline uint64_t level_len(const lsm_t h, int i) { return static_cast<uint64_t>(h->b) << i; }
 
@@ -335,6 +400,7 @@ void release_all(lsm_t h) {
     dev_free(h, h->q_status, scan_status_words(static_cast<uint32_t>(h->q_cap)) * sizeof(uint64_t));
   }
   dev_free(h, h->q_bounds, h->q_bwords * sizeof(uint32_t));
+  dev_free(h, h->work, h->work_bytes);
   if (h->h_pinned) (void)hipHostFree(h->h_pinned);
   if (h->skew_host) (void)hipHostFree(h->skew_host);
   if (h->progress_host) (void)hipHostFree(h->progress_host);
@@ -1141,35 +1207,23 @@ lsm_status_t lsm_bulk_insert(lsm_t h, const uint32_t* d_keys, const uint32_t* d_
   // Scratch: the sort's ping-pong and look-back words for the largest new
   // part; two merge buffers when a level takes over old levels.
   const size_t meta_bytes = sort_meta_words(static_cast<uint32_t>(max_new)) * sizeof(uint32_t);
-  void* st[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // [buffer][kv, val]
-  void* mg[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
-  void* meta = nullptr;
-  auto release = [&]() {
-    for (int q = 0; q < 2; ++q)
-      for (int c = 0; c < 2; ++c) {
-        dev_free(h, st[q][c], max_new * sizeof(uint32_t));
-        dev_free(h, mg[q][c], max_level * sizeof(uint32_t));
-      }
-    dev_free(h, meta, meta_bytes);
-  };
-  for (int q = 0; q < 2 && s == LSM_OK; ++q)
-    for (int c = 0; c < 2 && s == LSM_OK; ++c) {
-      s = dev_alloc(h, &st[q][c], max_new * sizeof(uint32_t));
-      if (s == LSM_OK && merges) s = dev_alloc(h, &mg[q][c], max_level * sizeof(uint32_t));
+  WorkArea wk(h);
+  int st[2][2], mg[2][2] = {};  // parts: [buffer][kv, val]
+  for (int q = 0; q < 2; ++q)
+    for (int c = 0; c < 2; ++c) {
+      st[q][c] = wk.add(max_new * sizeof(uint32_t));
+      if (merges) mg[q][c] = wk.add(max_level * sizeof(uint32_t));
     }
-  if (s == LSM_OK) s = dev_alloc(h, &meta, meta_bytes);
+  const int meta_part = wk.add(meta_bytes);
+  s = wk.claim();
   for (int q = 0; q < np && s == LSM_OK; ++q) s = ensure_level(h, plan[q].level);
-  if (s != LSM_OK) {
-    release();
-    return s;
-  }
-  s = settle(h);  // allocates nothing now
-  if (s != LSM_OK || h->r != r0) {
-    release();
-    return s != LSM_OK ? s : LSM_EHIP;
-  }
-  auto u32 = [](void* p) { return static_cast<uint32_t*>(p); };
-  hipError_t e = hipMemsetAsync(meta, 0, meta_bytes, h->stream);
+  if (s == LSM_OK) s = settle(h);  // allocates nothing now
+  if (s != LSM_OK) return s;
+  if (h->r != r0) return LSM_EHIP;
+  uint32_t* meta = wk.part(meta_part);
+  // Only the digit histograms have to start at zero; every other word is
+  // written or cleared by the sort that reads it.
+  hipError_t e = hipMemsetAsync(meta, 0, 2ull * kMaxPasses * kRadix * sizeof(uint32_t), h->stream);
   uint64_t merged = 0, sorted = 0;
   int parity = 0;
   for (int q = 0; q < np && e == hipSuccess; ++q) {
@@ -1182,17 +1236,19 @@ lsm_status_t lsm_bulk_insert(lsm_t h, const uint32_t* d_keys, const uint32_t* d_
     sa.src = BatchSrc{d_keys + e0, d_vals + e0, nullptr, static_cast<uint32_t>(avail),
                       static_cast<uint32_t>(len), static_cast<int>(kInsert)};
     sort_params(h, kInsert, sa);
-    sa.meta = sort_meta_carve(u32(meta), static_cast<uint32_t>(len), parity, 0);
-    sa.tmp_kv[0] = u32(st[0][0]);
-    sa.tmp_val[0] = u32(st[0][1]);
-    sa.tmp_kv[1] = u32(st[1][0]);
-    sa.tmp_val[1] = u32(st[1][1]);
-    sa.out_kv = p.n_old == 0 ? h->lvl_kv[i] : u32(mg[0][0]);
-    sa.out_val = p.n_old == 0 ? h->lvl_val[i] : u32(mg[0][1]);
+    sa.meta = sort_meta_carve(meta, static_cast<uint32_t>(len), parity, 0);
+    sa.tmp_kv[0] = wk.part(st[0][0]);
+    sa.tmp_val[0] = wk.part(st[0][1]);
+    sa.tmp_kv[1] = wk.part(st[1][0]);
+    sa.tmp_val[1] = wk.part(st[1][1]);
+    sa.out_kv = p.n_old == 0 ? h->lvl_kv[i] : wk.part(mg[0][0]);
+    sa.out_val = p.n_old == 0 ? h->lvl_val[i] : wk.part(mg[0][1]);
     sa.out_fence = p.n_old == 0 ? h->lvl_fence[i] : nullptr;
     sa.out_n = static_cast<uint32_t>(len);
     sa.path = sort_path(h, sa.meta.num_sort_tiles);
-    sa.skew_out = h->skew_dev;
+    // No hint: it speaks of sorts of b elements, and the record behind it is
+    // that of the handle's own scratch.
+    sa.skew_out = nullptr;
     Timed ts[1 + kMaxPasses];
     KTimer tt[1 + kMaxPasses];
     const int nk = sort_kernel_count(sa);
@@ -1213,8 +1269,8 @@ lsm_status_t lsm_bulk_insert(lsm_t h, const uint32_t* d_keys, const uint32_t* d_
     for (int x = 0; x < p.n_old && e == hipSuccess; ++x) {
       const int j = p.old[x];
       const bool last = x == p.n_old - 1;
-      uint32_t* ok = last ? h->lvl_kv[i] : u32(mg[(x + 1) & 1][0]);
-      uint32_t* ov = last ? h->lvl_val[i] : u32(mg[(x + 1) & 1][1]);
+      uint32_t* ok = last ? h->lvl_kv[i] : wk.part(mg[(x + 1) & 1][0]);
+      uint32_t* ov = last ? h->lvl_val[i] : wk.part(mg[(x + 1) & 1][1]);
       const uint64_t lj = level_len(h, j);
       Timed mt;
       e = launch_merge(ak, av, static_cast<uint32_t>(alen), h->lvl_kv[j], h->lvl_val[j],
@@ -1228,7 +1284,6 @@ lsm_status_t lsm_bulk_insert(lsm_t h, const uint32_t* d_keys, const uint32_t* d_
     }
   }
   const hipError_t e2 = hipStreamSynchronize(h->stream);
-  release();
   if (e != hipSuccess || e2 != hipSuccess) return LSM_EHIP;
   for (int q = 0; q < np; ++q) h->digit_shift[plan[q].level] = -1;
   h->r = r1;
@@ -1270,29 +1325,19 @@ lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid) {
   // Scratch: one or two merge buffers (kv + val), the tiles' offsets.
   const size_t bytes = total * sizeof(uint32_t);
   const uint32_t tiles = clean_tiles(n);
-  void* tk[2] = {nullptr, nullptr};
-  void* tv[2] = {nullptr, nullptr};
-  void* toff = nullptr;
   const int nbuf = m >= 3 ? 2 : 1;
-  auto release = [&]() {
-    for (int q = 0; q < 2; ++q) {
-      dev_free(h, tk[q], bytes);
-      dev_free(h, tv[q], bytes);
-    }
-    dev_free(h, toff, (tiles + 1ull) * sizeof(uint64_t));
-  };
-  for (int q = 0; q < nbuf && s == LSM_OK; ++q) {
-    s = dev_alloc(h, &tk[q], bytes);
-    if (s == LSM_OK) s = dev_alloc(h, &tv[q], bytes);
-  }
-  if (s == LSM_OK) s = dev_alloc(h, &toff, (tiles + 1ull) * sizeof(uint64_t));
+  WorkArea wk(h);
+  int part[2][2];
+  for (int q = 0; q < nbuf; ++q)
+    for (int c = 0; c < 2; ++c) part[q][c] = wk.add(bytes);
+  const int off_part = wk.add((tiles + 1ull) * sizeof(uint64_t));
+  s = wk.claim();
   if (s == LSM_OK) s = ensure_query_scratch(h, tiles);
   if (s == LSM_OK) s = settle(h);  // allocates nothing now
   if (s == LSM_OK && h->r != r_all) s = LSM_EHIP;
-  if (s != LSM_OK) {
-    release();
-    return s;
-  }
+  if (s != LSM_OK) return s;
+  uint32_t* tk[2] = {wk.part(part[0][0]), nbuf > 1 ? wk.part(part[1][0]) : nullptr};
+  uint32_t* tv[2] = {wk.part(part[0][1]), nbuf > 1 ? wk.part(part[1][1]) : nullptr};
   hipError_t e = hipSuccess;
   const uint32_t* ak = h->lvl_kv[occ[0]];
   const uint32_t* av = h->lvl_val[occ[0]];
@@ -1300,14 +1345,14 @@ lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid) {
   if (m == 1) {
     e = hipMemcpyAsync(tk[0], ak, bytes, hipMemcpyDeviceToDevice, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(tv[0], av, bytes, hipMemcpyDeviceToDevice, h->stream);
-    ak = static_cast<uint32_t*>(tk[0]);
-    av = static_cast<uint32_t*>(tv[0]);
+    ak = tk[0];
+    av = tv[0];
   }
   for (int k = 1; k < m && e == hipSuccess; ++k) {
     const int i = occ[k];
     const uint64_t len = level_len(h, i);
-    uint32_t* ok = static_cast<uint32_t*>(tk[(k - 1) & 1]);
-    uint32_t* ov = static_cast<uint32_t*>(tv[(k - 1) & 1]);
+    uint32_t* ok = tk[(k - 1) & 1];
+    uint32_t* ov = tv[(k - 1) & 1];
     Timed mt;
     e = launch_merge(ak, av, static_cast<uint32_t>(alen), h->lvl_kv[i], h->lvl_val[i],
                      static_cast<uint32_t>(len), ok, ov, nullptr, kDefaultMergeVariant, h->stream,
@@ -1316,7 +1361,7 @@ lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid) {
     av = ov;
     alen += len;
   }
-  uint64_t* tile_off = static_cast<uint64_t*>(toff);
+  uint64_t* tile_off = reinterpret_cast<uint64_t*>(wk.part(off_part));
   Timed t1, t2;
   if (e == hipSuccess)
     e = launch_clean_count(ak, n, h->q_counts, h->q_status, scan_status_words(tiles), h->stream,
@@ -1330,7 +1375,6 @@ lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid) {
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(h->stream);
-    release();
     return LSM_EHIP;
   }
   const uint64_t v = *reinterpret_cast<volatile uint64_t*>(h->h_pinned);
@@ -1352,7 +1396,6 @@ lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid) {
     e = launch_clean_pad(d, v, r2 * h->b, h->stream,
                          timer(h, t4, kKClean, r2 * h->b - v, 8.0 * (r2 * h->b - v)));
   const hipError_t e2 = hipStreamSynchronize(h->stream);
-  release();
   if (e != hipSuccess || e2 != hipSuccess) return LSM_EHIP;
   for (int i = 0; i < kMaxLevels; ++i)
     if ((r2 >> i) & 1u) h->digit_shift[i] = -1;
