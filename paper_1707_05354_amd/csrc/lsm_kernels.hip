@@ -233,98 +233,223 @@ __device__ __forceinline__ uint32_t octet_sum(uint32_t x) {
   return x;
 }
 
-// fenced_bound for a whole wave at once, the eight lanes of an octet
-// searching the octet's eight queries together: at every tree level lane s
-// of the octet reads bytes 16 s .. 16 s + 15 of each of the eight queries'
-// 128-byte lines, so a load instruction of the wave reads eight whole lines
-// instead of 64 scattered 16-byte pieces of 64 lines (the per-lane search
-// keeps the texture addresser busy nearly all the time).  Entry counts are
-// summed over the octet.  Each lane passes its own key and receives its own
-// bound; every lane of the wave must call it (lanes without a query pass
-// any key and ignore the result).
-template <bool kUpper>
-__device__ __forceinline__ uint32_t octet_bound(const uint32_t* kv, const uint32_t* tree,
-                                                uint32_t n, uint32_t k) {
-  const uint32_t lane = lane_id(), sub = lane & 7u, ob = lane & ~7u;
-  uint32_t kq[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) kq[j] = __shfl(k, static_cast<int>(ob) + j, 64);
-  if (n == 0) return 0u;
-  auto qual = [](uint32_t x, uint32_t key) { return kUpper ? x <= key : x < key; };
-  uint64_t off = 0, c = (static_cast<uint64_t>(n) + 31) / 32;
-  int t = 1;
-  while (c > 32) {
-    off += fence_pad(c);
-    c = (c + 31) / 32;
-    ++t;
+// The upper part of every occupied level's fence tree in LDS: of each level the
+// lowest tree level that has at most `cap` entries, the levels' parts one
+// after another, each in whole blocks of 64 words.  A search then
+// starts there with a binary search of its own lane and reads only the tree
+// levels below from memory: with ten levels of 2^16 .. 2^25 elements 24
+// lines a query instead of 45.  cap is halved from kTopEntries until all parts
+// fit (at most kTopWords, 16 KB: with 32 KB lookups are no faster and the order queries,
+// which keep cursors beside the tops, take 356 us instead of 262).
+constexpr uint32_t kTopEntries = 2048;
+constexpr uint32_t kTopWords = 4096;
+static_assert(kMaxLevels * 64 <= kTopWords, "32 levels of at most 32 entries always fit");
+struct TopSet {
+  uint32_t at[kMaxLevels];   // first LDS word of the level's part
+  uint32_t cnt[kMaxLevels];  // its entries
+  uint32_t off[kMaxLevels];  // where that tree level starts in the fence tree
+  uint32_t t[kMaxLevels];    // which tree level it is
+  uint32_t words;            // LDS words of all parts
+};
+inline TopSet top_set(const LevelSet& lv, uint32_t words) {
+  TopSet s{};
+  for (uint64_t cap = kTopEntries;; cap /= 2) {
+    s.words = 0;
+    for (int l = 0; l < lv.count; ++l) {
+      uint64_t off = 0, c = (static_cast<uint64_t>(lv.len[l]) + 31) / 32;
+      uint32_t t = 1;
+      while (c > cap) {
+        off += fence_pad(c);
+        c = (c + 31) / 32;
+        ++t;
+      }
+      s.at[l] = s.words;
+      s.cnt[l] = static_cast<uint32_t>(c);
+      s.off[l] = static_cast<uint32_t>(off);
+      s.t[l] = t;
+      s.words += (static_cast<uint32_t>(c) + 63u) & ~63u;
+    }
+    if (s.words <= words || cap <= 32) return s;
   }
-  uint32_t g[8];
-  {
-    // The root line, the same for every query.
-    const uint4 w = *reinterpret_cast<const uint4*>(tree + off + 4u * sub);
-    const uint32_t e4[4] = {w.x, w.y, w.z, w.w};
+}
+
+// Entry i of a part stands at word i with its low six bits exclusive-ored by
+// its block: the probes of a binary search are multiples of a power of two
+// apart, which would all fall on one LDS bank.
+__device__ __forceinline__ uint32_t top_word(uint32_t i) { return i ^ ((i >> 6) & 63u); }
+
+// Loads every part (all threads of the work-group; kN waves).  The blocks of
+// 64 words are dealt to the waves in turn, eight in flight.
+template <int kN>
+__device__ __forceinline__ void load_tops(const LevelSet& lv, const TopSet& ts, uint32_t* top) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const uint32_t blocks = ts.words >> 6;
+  for (uint32_t b0 = wave; b0 < blocks; b0 += 8 * kN) {
+    uint32_t v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      uint32_t cnt = 0;
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t blk = b0 + u * kN;
+      v[u] = 0u;
+      if (blk < blocks) {
+        int l = 0;
+        while (l + 1 < lv.count && ts.at[l + 1] <= blk * 64u) ++l;
+        const uint32_t i = blk * 64u - ts.at[l] + lane;
+        if (i < ts.cnt[l]) v[u] = lv.fence[l][ts.off[l] + i];
+      }
+    }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) cnt += (4u * sub + r < c && qual(e4[r], kq[j])) ? 1u : 0u;
-      g[j] = octet_sum(cnt);
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t blk = b0 + u * kN;
+      if (blk < blocks) {
+        int l = 0;
+        while (l + 1 < lv.count && ts.at[l + 1] <= blk * 64u) ++l;
+        top[ts.at[l] + top_word(blk * 64u - ts.at[l] + lane)] = v[u];
+      }
     }
   }
-  for (--t; t >= 1; --t) {
-    const uint64_t ct = (static_cast<uint64_t>(n) + (1ull << (5 * t)) - 1) >> (5 * t);
-    off -= fence_pad(ct);
+  __syncthreads();
+}
+
+// Number of the cnt entries of a part that are < k (upper: <= k).
+template <bool kUpper>
+__device__ __forceinline__ uint32_t top_count(const uint32_t* part, uint32_t cnt, uint32_t k) {
+  uint32_t p = 0;
+  for (uint32_t step = 1u << (31 - __builtin_clz(cnt)); step > 0; step >>= 1) {
+    const uint32_t q = p + step;
+    const uint32_t x = part[top_word((q < cnt ? q : cnt) - 1u)];
+    p = (q <= cnt && (kUpper ? x <= k : x < k)) ? q : p;
+  }
+  return p;
+}
+
+// x of lane j of the octet, in all eight lanes.
+template <int kJ>
+__device__ __forceinline__ uint32_t octet_lane(uint32_t x) {
+  return static_cast<uint32_t>(
+      __builtin_amdgcn_ds_swizzle(static_cast<int>(x), (kJ << 5) | 0x18));
+}
+__device__ __forceinline__ void octet_lanes(uint32_t x, uint32_t (&q)[8]) {
+  q[0] = octet_lane<0>(x);
+  q[1] = octet_lane<1>(x);
+  q[2] = octet_lane<2>(x);
+  q[3] = octet_lane<3>(x);
+  q[4] = octet_lane<4>(x);
+  q[5] = octet_lane<5>(x);
+  q[6] = octet_lane<6>(x);
+  q[7] = octet_lane<7>(x);
+}
+
+// fenced_bound for a whole wave at once, from the level's part of the LDS tops
+// on: each lane counts its own key there, then the eight lanes of an octet
+// search the octet's eight queries together: at every tree level lane s of the
+// octet reads bytes 16 s .. 16 s + 15 of each of the eight queries' 128-byte
+// lines, so a load instruction of the wave reads eight whole lines instead of
+// 64 scattered 16-byte pieces of 64 lines (a per-lane search keeps the texture
+// addresser busy nearly all the time).  Entry counts are summed over the
+// octet.  kq: the octet's keys (octet_lanes of k).  Each lane passes its own
+// key and receives its own bound; every lane of the wave must call it (lanes
+// without a query pass any key and ignore the result).  With kFind, *hit
+// receives whether the element at the bound can hold key k: exactly, or true
+// when it stands in the next line (one time in 32).
+template <bool kUpper, bool kFind>
+__device__ __forceinline__ uint32_t octet_bound(const LevelSet& lv, const TopSet& ts,
+                                                const uint32_t* top, int l, uint32_t k,
+                                                const uint32_t (&kq)[8], bool* hit) {
+  static_assert(!kUpper || !kFind, "the bound of a key that is looked for is the lower one");
+  const uint32_t lane = lane_id(), sub = lane & 7u;
+  const uint32_t n = lv.len[l];
+  if (n == 0) {
+    if (kFind) *hit = false;
+    return 0u;
+  }
+  uint32_t g[8];
+  octet_lanes(top_count<kUpper>(top + ts.at[l], ts.cnt[l], k), g);
+  const uint32_t* tree = lv.fence[l];
+  uint32_t off = ts.off[l];
+  // A tree level's answer lies in the line that starts at its parent's entry
+  // g - 1; the line's first entry qualifies with its parent, and with g = 0
+  // no entry of line 0 qualifies, so a plain count serves both.
+  for (uint32_t t = ts.t[l] - 1; t >= 1; --t) {
+    const uint32_t ct = static_cast<uint32_t>((static_cast<uint64_t>(n) + (1ull << (5 * t)) - 1) >> (5 * t));
+    off -= static_cast<uint32_t>(fence_pad(ct));
+    const uint32_t* line = tree + off + 4u * sub;
     uint4 w[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const uint32_t base = g[j] > 0 ? (g[j] - 1) * 32u : 0u;
-      w[j] = *reinterpret_cast<const uint4*>(tree + off + base + 4u * sub);
+      g[j] = g[j] > 0 ? (g[j] - 1u) * 32u : 0u;  // the line's first entry
+      w[j] = *reinterpret_cast<const uint4*>(line + g[j]);
     }
+    if ((ct & 31u) == 0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t base = g[j] > 0 ? (g[j] - 1) * 32u : 0u;
-      const uint32_t lim = (base + 32u < ct) ? 32u : static_cast<uint32_t>(ct - base);
-      const uint32_t e4[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
-      uint32_t cnt = 0;
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t e4[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
+        uint32_t cnt = 0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t i = 4u * sub + r;
-        cnt += (i >= 1u && i < lim && qual(e4[r], kq[j])) ? 1u : 0u;
+        for (int r = 0; r < 4; ++r) cnt += (kUpper ? e4[r] <= kq[j] : e4[r] < kq[j]) ? 1u : 0u;
+        g[j] += octet_sum(cnt);
       }
-      const uint32_t sum = octet_sum(cnt);
-      g[j] = g[j] > 0 ? base + sum + 1u : 0u;
+    } else {  // the last line is partly filled
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t e4[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          cnt += (g[j] + 4u * sub + r < ct && (kUpper ? e4[r] <= kq[j] : e4[r] < kq[j])) ? 1u : 0u;
+        g[j] += octet_sum(cnt);
+      }
     }
   }
-  // The level's own line (the last one may be partial: read what exists).
+  // The level's own line.  Key variables are compared whole: below 2 k, or at
+  // most 2 k + 1.  (Keys from 2^31 on are above every element.)
+  const uint32_t* kv = lv.kv[l];
   uint4 w[8];
+  if ((n & 31u) == 0) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t i0 = (g[j] > 0 ? (g[j] - 1) * 32u : 0u) + 4u * sub;
-    if (i0 + 4u <= n) {
-      w[j] = *reinterpret_cast<const uint4*>(kv + i0);
-    } else {
-      w[j].x = i0 < n ? kv[i0] : 0u;
-      w[j].y = i0 + 1u < n ? kv[i0 + 1u] : 0u;
-      w[j].z = i0 + 2u < n ? kv[i0 + 2u] : 0u;
-      w[j].w = 0u;
+    for (int j = 0; j < 8; ++j) {
+      g[j] = g[j] > 0 ? (g[j] - 1u) * 32u : 0u;
+      w[j] = *reinterpret_cast<const uint4*>(kv + g[j] + 4u * sub);
+    }
+  } else {  // the last line may be partial: read what exists
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      g[j] = g[j] > 0 ? (g[j] - 1u) * 32u : 0u;
+      const uint32_t i0 = g[j] + 4u * sub;
+      if (i0 + 4u <= n) {
+        w[j] = *reinterpret_cast<const uint4*>(kv + i0);
+      } else {
+        w[j].x = i0 < n ? kv[i0] : 0u;
+        w[j].y = i0 + 1u < n ? kv[i0 + 1u] : 0u;
+        w[j].z = i0 + 2u < n ? kv[i0 + 2u] : 0u;
+        w[j].w = 0u;
+      }
     }
   }
   uint32_t res = 0;
+  bool h = false;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const uint32_t base = g[j] > 0 ? (g[j] - 1) * 32u : 0u;
-    const uint32_t lim = (base + 32u <= n) ? 32u : n - base;
     const uint32_t e4[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
-    uint32_t cnt = 0;
+    const uint32_t kl = kq[j] << 1, ku = kl | 1u;
+    uint32_t lt = 0, le = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const uint32_t i = 4u * sub + r;
-      cnt += (i >= 1u && i < lim && qual(e4[r] >> 1, kq[j])) ? 1u : 0u;
+      const bool in = (n & 31u) == 0 || g[j] + 4u * sub + r < n;
+      if (!kUpper) lt += (in && e4[r] < kl) ? 1u : 0u;
+      if (kUpper || kFind) le += (in && e4[r] <= ku) ? 1u : 0u;
     }
-    const uint32_t sum = octet_sum(cnt);
-    const uint32_t b = g[j] > 0 ? base + sum + 1u : 0u;
-    res = (sub == static_cast<uint32_t>(j)) ? b : res;
+    const uint32_t sum = octet_sum(kUpper ? le : kFind ? (lt | (le << 16)) : lt);
+    if (sub == static_cast<uint32_t>(j)) {
+      res = g[j] + (kFind ? sum & 0xFFFFu : sum);
+      if (kFind) h = (sum >> 16) != (sum & 0xFFFFu) || (sum & 0xFFFFu) == 32u;
+    }
   }
+  if (k > 0x7FFFFFFFu) {
+    res = n;
+    h = false;
+  }
+  if (kFind) *hit = h;
   return res;
 }
 
@@ -1965,35 +2090,47 @@ __global__ __launch_bounds__(kThreads) void k_fill_runs(uint32_t* a_kv, uint32_t
 }
 
 // ------------------------------------------------------------ queries
-__global__ __launch_bounds__(kQueryThreads) void k_lookup(LevelSet lv, const uint32_t* q,
-                                                          uint32_t nq, uint32_t* out_val,
-                                                          uint8_t* out_found) {
-  // Every lane stays until the wave is done: the searches are wave-wide.
-  const uint32_t i = blockIdx.x * kQueryThreads + threadIdx.x;
-  const bool active = i < nq;
-  const uint32_t k = active ? q[i] : 0u;
-  uint32_t v = 0u;
-  uint8_t f = 0;
-  bool done = !active;
-  for (int l = 0; l < lv.count; ++l) {
-    if (ballot(!done) == 0) break;
-    const uint32_t* kv = lv.kv[l];
-    const uint32_t n = lv.len[l];
-    const uint32_t p = octet_bound<false>(kv, lv.fence[l], n, k);
-    if (!done && p < n) {
-      const uint32_t x = kv[p];
-      if ((x >> 1) == k) {
-        if (x & 1u) {
-          v = lv.val[l][p];
-          f = 1;
+// What bounds lookups: with ten levels (2^26 elements) 12 lines a query come
+// from memory, and 2^22 queries take 1.04 ms, 6.3 TB/s of such random lines
+// (1.39 ms with whole descents: then the addresser and the longer chain of
+// dependent loads bound it too); with one level 212 us (244).  Five waves a
+// SIMD hide the chain; at four (98 registers) ten levels take 1.10 ms.
+__global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(LevelSet lv, TopSet ts,
+                                                             const uint32_t* q, uint32_t nq,
+                                                             uint32_t* out_val,
+                                                             uint8_t* out_found) {
+  extern __shared__ uint32_t top[];
+  load_tops<kQueryThreads / 64>(lv, ts, top);
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
+    // Every lane stays until the wave is done: the searches are wave-wide.
+    const uint64_t i = q0 + threadIdx.x;
+    const bool active = i < nq;
+    const uint32_t k = active ? q[i] : 0u;
+    uint32_t kq[8];
+    octet_lanes(k, kq);
+    uint32_t v = 0u;
+    uint8_t f = 0;
+    bool done = !active;
+    for (int l = 0; l < lv.count; ++l) {
+      if (ballot(!done) == 0) break;
+      bool hit;
+      const uint32_t p = octet_bound<false, true>(lv, ts, top, l, k, kq, &hit);
+      if (!done && hit && p < lv.len[l]) {
+        const uint32_t x = lv.kv[l][p], y = lv.val[l][p];
+        if ((x >> 1) == k) {
+          if (x & 1u) {
+            v = y;
+            f = 1;
+          }
+          done = true;  // the newest instance decides, tombstone or not
         }
-        done = true;  // the newest instance decides, tombstone or not
       }
     }
-  }
-  if (active) {
-    out_val[i] = v;
-    out_found[i] = f;
+    if (active) {
+      out_val[i] = v;
+      out_found[i] = f;
+    }
   }
 }
 
@@ -2033,12 +2170,15 @@ __device__ __forceinline__ uint32_t skip_run(const uint32_t* kv, uint32_t c, uin
 // this; for k1 > k2 the walks then find no candidate (every key from the
 // lower bound on is above k2).
 template <int kW>
-__device__ __forceinline__ void level_bounds(const LevelSet& lv, uint32_t k1,
+__device__ __forceinline__ void level_bounds(const LevelSet& lv, const TopSet& ts,
+                                             const uint32_t* top, uint32_t k1,
                                              uint32_t (&cur)[kW]) {
+  uint32_t kq[8];
+  octet_lanes(k1, kq);
 #pragma unroll
   for (int q = 0; q < kW; ++q) cur[q] = 0u;
   for (int l = 0; l < lv.count && l < kW; ++l) {
-    const uint32_t lo = octet_bound<false>(lv.kv[l], lv.fence[l], lv.len[l], k1);
+    const uint32_t lo = octet_bound<false, false>(lv, ts, top, l, k1, kq, nullptr);
 #pragma unroll
     for (int q = 0; q < kW; ++q) {
       if (q == l) cur[q] = lo;
@@ -2134,41 +2274,49 @@ __device__ __forceinline__ uint32_t range_walk(const LevelSet& lv, uint32_t (&cu
 // bounds [lower_bound(lo), upper_bound(hi)) are also stored (two words per
 // query) for the emission pass.
 template <int kW>
-__global__ __launch_bounds__(kQueryThreads) void k_count(LevelSet lv, const uint32_t* lo,
-                                                         const uint32_t* hi, uint32_t nq,
-                                                         uint32_t* counts, uint64_t* scan_status,
+__global__ __launch_bounds__(kQueryThreads) void k_count(LevelSet lv, TopSet ts,
+                                                         const uint32_t* lo, const uint32_t* hi,
+                                                         uint32_t nq, uint32_t* counts,
+                                                         uint64_t* scan_status,
                                                          uint64_t scan_words, uint32_t* bounds) {
-  const uint64_t gi = static_cast<uint64_t>(blockIdx.x) * kQueryThreads + threadIdx.x;
-  if (scan_status != nullptr) {
-    for (uint64_t w = gi; w < scan_words; w += static_cast<uint64_t>(gridDim.x) * kQueryThreads)
-      scan_status[w] = 0ull;
-  }
-  // Every lane takes part in the wave-wide descents; lanes without a query
-  // search the empty range [1, 0].  Several levels: with bounds non-null,
-  // each query's per-level cursors (lower bounds) are stored level-major
-  // (word l * nq + query) for the emission pass.
-  const bool active = gi < nq;
-  const uint32_t k1 = active ? lo[gi] : 1u, k2 = active ? hi[gi] : 0u;
-  if constexpr (kW == 1) {
-    // Both bounds by descents, so the scan reads only the candidates.
-    uint32_t p = octet_bound<false>(lv.kv[0], lv.fence[0], lv.len[0], k1);
-    uint32_t e = octet_bound<true>(lv.kv[0], lv.fence[0], lv.len[0], k2);
-    if (!active) return;
-    uint32_t c = 0;
-    if (k1 <= k2) c = count_run_starts(lv.kv[0], p, e, k2, &e);
-    else p = e = 0;
-    if (bounds != nullptr) reinterpret_cast<uint2*>(bounds)[gi] = make_uint2(p, e);
-    counts[gi] = c;
-  } else {
-    uint32_t cur[kW];
-    level_bounds<kW>(lv, k1, cur);
-    if (bounds != nullptr && active) {
+  extern __shared__ uint32_t top[];
+  const uint64_t threads = static_cast<uint64_t>(gridDim.x) * kQueryThreads;
+  const uint64_t g0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads;
+  if (scan_status != nullptr)
+    for (uint64_t w = g0 + threadIdx.x; w < scan_words; w += threads) scan_status[w] = 0ull;
+  load_tops<kQueryThreads / 64>(lv, ts, top);
+  for (uint64_t q0 = g0; q0 < nq; q0 += threads) {
+    // Every lane takes part in the wave-wide descents; lanes without a query
+    // search the empty range [1, 0].  Several levels: with bounds non-null,
+    // each query's per-level cursors (lower bounds) are stored level-major
+    // (word l * nq + query) for the emission pass.
+    const uint64_t gi = q0 + threadIdx.x;
+    const bool active = gi < nq;
+    const uint32_t k1 = active ? lo[gi] : 1u, k2 = active ? hi[gi] : 0u;
+    if constexpr (kW == 1) {
+      // Both bounds by descents, so the scan reads only the candidates.
+      uint32_t kq[8];
+      octet_lanes(k1, kq);
+      uint32_t p = octet_bound<false, false>(lv, ts, top, 0, k1, kq, nullptr);
+      octet_lanes(k2, kq);
+      uint32_t e = octet_bound<true, false>(lv, ts, top, 0, k2, kq, nullptr);
+      if (!active) continue;
+      uint32_t c = 0;
+      if (k1 <= k2) c = count_run_starts(lv.kv[0], p, e, k2, &e);
+      else p = e = 0;
+      if (bounds != nullptr) reinterpret_cast<uint2*>(bounds)[gi] = make_uint2(p, e);
+      counts[gi] = c;
+    } else {
+      uint32_t cur[kW];
+      level_bounds<kW>(lv, ts, top, k1, cur);
+      if (bounds != nullptr && active) {
 #pragma unroll
-      for (int q = 0; q < kW; ++q)
-        if (q < lv.count) bounds[static_cast<size_t>(q) * nq + gi] = cur[q];
+        for (int q = 0; q < kW; ++q)
+          if (q < lv.count) bounds[static_cast<size_t>(q) * nq + gi] = cur[q];
+      }
+      const uint32_t c = range_walk<kW>(lv, cur, k2);
+      if (active) counts[gi] = c;
     }
-    const uint32_t c = range_walk<kW>(lv, cur, k2);
-    if (active) counts[gi] = c;
   }
 }
 
@@ -2187,7 +2335,8 @@ struct WalkMany {
 // for query i, read only when `use`) or from wave-wide descents (every lane
 // of the wave calls it then).
 template <int kW, bool kSearch>
-__device__ __forceinline__ void walk_init(const LevelSet& lv, uint32_t k1, uint32_t k2,
+__device__ __forceinline__ void walk_init(const LevelSet& lv, const TopSet& ts,
+                                          const uint32_t* top, uint32_t k1, uint32_t k2,
                                           const uint32_t* cursors, uint32_t nq, uint32_t i,
                                           bool use, WalkMany<kW>& w) {
   w.k2 = k2;
@@ -2196,7 +2345,7 @@ __device__ __forceinline__ void walk_init(const LevelSet& lv, uint32_t k1, uint3
     for (int q = 0; q < kW; ++q)
       w.cur[q] = (use && q < lv.count) ? cursors[static_cast<size_t>(q) * nq + i] : 0u;
   } else {
-    level_bounds<kW>(lv, k1, w.cur);
+    level_bounds<kW>(lv, ts, top, k1, w.cur);
   }
 #pragma unroll
   for (int l = 0; l < kW; ++l) w.ck[l] = cand_key(lv.kv[l], w.cur[l], lv.len[l], k2);
@@ -2254,7 +2403,8 @@ constexpr uint32_t kEmitChunk = 512;
 constexpr int kQueryWaves = kQueryThreads / 64;
 
 template <int kW, bool kSearch>
-__global__ __launch_bounds__(kQueryThreads) void k_range_emit(LevelSet lv, const uint32_t* lo,
+__global__ __launch_bounds__(kQueryThreads) void k_range_emit(LevelSet lv, TopSet ts,
+                                                              const uint32_t* lo,
                                                               const uint32_t* hi, uint32_t nq,
                                                               const uint64_t* offsets,
                                                               const uint32_t* cursors,
@@ -2262,6 +2412,8 @@ __global__ __launch_bounds__(kQueryThreads) void k_range_emit(LevelSet lv, const
                                                               uint32_t* out_vals, uint64_t cap) {
   __shared__ uint32_t sk[kQueryWaves][kEmitChunk], sv[kQueryWaves][kEmitChunk];
   __shared__ uint32_t s_rounds[kQueryWaves];
+  extern __shared__ uint32_t top[];
+  if (kSearch) load_tops<kQueryWaves>(lv, ts, top);
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t i = blockIdx.x * kQueryThreads + tid;
   const uint32_t q0 = blockIdx.x * kQueryThreads + wave * 64;
@@ -2286,7 +2438,7 @@ __global__ __launch_bounds__(kQueryThreads) void k_range_emit(LevelSet lv, const
   WalkMany<kW> w;
   // Stored cursors (only the queries that emit read theirs), or wave-wide
   // descents by every lane.
-  walk_init<kW, kSearch>(lv, fits ? lo[i] : 1u, fits ? hi[i] : 0u, cursors, nq, i, fits, w);
+  walk_init<kW, kSearch>(lv, ts, top, fits ? lo[i] : 1u, fits ? hi[i] : 0u, cursors, nq, i, fits, w);
   __syncthreads();
   uint32_t R = 0;
 #pragma unroll
@@ -2360,7 +2512,7 @@ __device__ __forceinline__ void emit_run_starts(const uint32_t* kv, const uint32
 // even for offsets corrupted by a timed-out scan.
 template <int kU, bool kSearch>
 __global__ __launch_bounds__(kQueryThreads) void k_range_emit_one(
-    LevelSet lv, const uint32_t* lo, const uint32_t* hi, uint32_t nq, const uint64_t* offsets,
+    LevelSet lv, TopSet ts, const uint32_t* lo, const uint32_t* hi, uint32_t nq, const uint64_t* offsets,
     const uint32_t* bounds, uint32_t* out_keys, uint32_t* out_vals, uint64_t cap) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t i = blockIdx.x * kQueryThreads + threadIdx.x;
@@ -2387,9 +2539,14 @@ __global__ __launch_bounds__(kQueryThreads) void k_range_emit_one(
   } else {
     // Wave-wide descents: every lane searches (an empty range if it emits
     // nothing).
+    extern __shared__ uint32_t top[];
+    load_tops<kQueryThreads / 64>(lv, ts, top);
     const uint32_t k1 = emit ? lo[i] : 1u, k2 = emit ? hi[i] : 0u;
-    p = octet_bound<false>(kv, lv.fence[0], len, k1);
-    e = octet_bound<true>(kv, lv.fence[0], len, k2);
+    uint32_t kq[8];
+    octet_lanes(k1, kq);
+    p = octet_bound<false, false>(lv, ts, top, 0, k1, kq, nullptr);
+    octet_lanes(k2, kq);
+    e = octet_bound<true, false>(lv, ts, top, 0, k2, kq, nullptr);
     if (!emit || k1 > k2) p = e = 0;
   }
   e = e < len ? e : len;
@@ -2499,110 +2656,137 @@ __global__ __launch_bounds__(kThreads) void k_scan(const uint32_t* counts, uint3
 // ------------------------------------------------------------ order queries
 constexpr uint32_t kMaxKey = 0x7FFFFFFFu;  // largest encodable original key
 
-// Successor: walk the level runs that start at upper_bound(q) in key order
-// (as range_walk does); the first key whose newest instance is a regular
-// element is the answer.
-__global__ __launch_bounds__(kQueryThreads) void k_successor(LevelSet lv, const uint32_t* q,
-                                                             uint32_t nq, uint32_t* out_key,
-                                                             uint32_t* out_val,
-                                                             uint8_t* out_found) {
-  const uint32_t i = blockIdx.x * kQueryThreads + threadIdx.x;
-  const bool active = i < nq;
-  const uint32_t k = active ? q[i] : 0u;
-  uint32_t rk = 0u, rv = 0u;
-  uint8_t f = 0;
-  // The first descents are wave-wide: every lane makes them.
-  uint32_t cur[kMaxLevels], ck[kMaxLevels];
-  const int L = lv.count;
-  for (int l = 0; l < L; ++l) {
-    cur[l] = octet_bound<true>(lv.kv[l], lv.fence[l], lv.len[l], k);
-    ck[l] = cur[l] < lv.len[l] ? (lv.kv[l][cur[l]] >> 1) : kNoKey;
-  }
-  if (!active) return;
-  if (k < kMaxKey) {
-    for (;;) {
-      uint32_t mk = kNoKey;
-      int mi = -1;
-      for (int l = 0; l < L; ++l) {
-        if (ck[l] < mk) {
-          mk = ck[l];
-          mi = l;
-        }
-      }
-      if (mi < 0) break;
-      if (lv.kv[mi][cur[mi]] & 1u) {
-        rk = mk;
-        rv = lv.val[mi][cur[mi]];
-        f = 1;
-        break;
-      }
-      for (int l = mi; l < L; ++l) {
-        if (ck[l] == mk) {
-          cur[l] = skip_run(lv.kv[l], cur[l], lv.len[l], mk);
-          ck[l] = cur[l] < lv.len[l] ? (lv.kv[l][cur[l]] >> 1) : kNoKey;
+// Successor: the smallest key at the levels' upper bounds of q.  Its newest
+// instance is the one of the first level that holds it; nearly always a
+// regular element, and the answer.  A tombstone drops the key: every level
+// skips its run of it, and the smallest key of the rest is next.  The cursors
+// stand in LDS (word l * kQueryThreads + thread), since an array indexed by
+// the level takes 148 registers: three waves a SIMD, 439 us for 2^20 queries
+// on seven levels; descending again from the dropped key takes 547.
+__global__ __launch_bounds__(kQueryThreads, 5) void k_successor(LevelSet lv, TopSet ts,
+                                                                const uint32_t* q, uint32_t nq,
+                                                                uint32_t* out_key,
+                                                                uint32_t* out_val,
+                                                                uint8_t* out_found) {
+  extern __shared__ uint32_t top[];
+  uint32_t* cur = top + ts.words + threadIdx.x;
+  load_tops<kQueryThreads / 64>(lv, ts, top);
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
+    const uint64_t i = q0 + threadIdx.x;
+    const uint32_t k = i < nq ? q[i] : kMaxKey;
+    uint32_t kq[8];
+    octet_lanes(k, kq);
+    uint32_t best = kNoKey, x = 0u;  // the smallest key and its newest instance
+    int level = 0;
+    for (int l = 0; l < lv.count; ++l) {
+      const uint32_t p = octet_bound<true, false>(lv, ts, top, l, k, kq, nullptr);
+      cur[l * kQueryThreads] = p;
+      if (p < lv.len[l]) {
+        const uint32_t y = lv.kv[l][p];
+        if ((y >> 1) < best) {  // ties: the newer level's stays
+          best = y >> 1;
+          x = y;
+          level = l;
         }
       }
     }
+    if (k >= kMaxKey) best = kNoKey;
+    while (best != kNoKey && (x & 1u) == 0u) {
+      const uint32_t gone = best;
+      best = kNoKey;
+      for (int l = 0; l < lv.count; ++l) {
+        const uint32_t* kv = lv.kv[l];
+        uint32_t p = cur[l * kQueryThreads];
+        if (p >= lv.len[l]) continue;
+        uint32_t y = kv[p];
+        if ((y >> 1) == gone) {
+          p = skip_run(kv, p, lv.len[l], gone);
+          cur[l * kQueryThreads] = p;
+          if (p >= lv.len[l]) continue;
+          y = kv[p];
+        }
+        if ((y >> 1) < best) {
+          best = y >> 1;
+          x = y;
+          level = l;
+        }
+      }
+    }
+    if (i < nq) {
+      const bool f = best != kNoKey;
+      out_key[i] = f ? best : 0u;
+      out_val[i] = f ? as_global(lv.val[level])[cur[level * kQueryThreads]] : 0u;
+      out_found[i] = f ? 1 : 0;
+    }
   }
-  out_key[i] = rk;
-  out_val[i] = rv;
-  out_found[i] = f;
 }
 
-// Predecessor: the mirror walk, downwards from lower_bound(q).  For the
-// largest remaining key, the newest instance is the first element of its run
-// in the smallest level holding it; a tombstone there discards the key, and
-// every level then drops its run of that key.
-__global__ __launch_bounds__(kQueryThreads) void k_predecessor(LevelSet lv, const uint32_t* q,
-                                                               uint32_t nq, uint32_t* out_key,
-                                                               uint32_t* out_val,
-                                                               uint8_t* out_found) {
-  const uint32_t i = blockIdx.x * kQueryThreads + threadIdx.x;
-  const bool active = i < nq;
-  const uint32_t k = active ? q[i] : 0u;
-  uint32_t rk = 0u, rv = 0u;
-  uint8_t f = 0;
-  // The first descents are wave-wide: every lane makes them.
-  uint32_t e[kMaxLevels], ck[kMaxLevels];  // ck = key just below e, or kNoKey
-  const int L = lv.count;
-  for (int l = 0; l < L; ++l) {
-    e[l] = octet_bound<false>(lv.kv[l], lv.fence[l], lv.len[l], k);
-    ck[l] = e[l] > 0u ? (lv.kv[l][e[l] - 1u] >> 1) : kNoKey;
-  }
-  if (!active) return;
-  if (k > 0u) {
-    for (;;) {
-      uint32_t mk = 0u;
-      int mi = -1;
-      for (int l = 0; l < L; ++l) {
-        if (ck[l] != kNoKey && (mi < 0 || ck[l] > mk)) {
-          mk = ck[l];
-          mi = l;
+// First element of the run of kv[c]'s key: nearly always c itself.
+__device__ __forceinline__ uint32_t run_start(const LevelSet& lv, int l, uint32_t c, uint32_t key) {
+  if (c == 0u || (as_global(lv.kv[l])[c - 1u] >> 1) != key) return c;
+  return fenced_bound(lv.kv[l], lv.fence[l], lv.len[l], key, false);
+}
+
+// Predecessor: the mirror walk, the largest key below the levels' lower bounds
+// of q; the newest instance is the first element of its run in the first level
+// that holds it.
+__global__ __launch_bounds__(kQueryThreads, 5) void k_predecessor(LevelSet lv, TopSet ts,
+                                                                  const uint32_t* q, uint32_t nq,
+                                                                  uint32_t* out_key,
+                                                                  uint32_t* out_val,
+                                                                  uint8_t* out_found) {
+  extern __shared__ uint32_t top[];
+  uint32_t* cur = top + ts.words + threadIdx.x;  // the candidate is the element below
+  load_tops<kQueryThreads / 64>(lv, ts, top);
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
+    const uint64_t i = q0 + threadIdx.x;
+    const uint32_t k = i < nq ? q[i] : 0u;
+    uint32_t kq[8];
+    octet_lanes(k, kq);
+    uint32_t best = kNoKey;  // the largest key, kNoKey for none
+    int level = 0;
+    for (int l = 0; l < lv.count; ++l) {
+      const uint32_t p = octet_bound<false, false>(lv, ts, top, l, k, kq, nullptr);
+      cur[l * kQueryThreads] = p;
+      if (p > 0u) {
+        const uint32_t key = lv.kv[l][p - 1u] >> 1;
+        if (best == kNoKey || key > best) {  // ties: the newer level's stays
+          best = key;
+          level = l;
         }
       }
-      if (mi < 0) break;
-      bool done = false;
-      for (int l = mi; l < L; ++l) {
-        if (ck[l] != mk) continue;
-        // The run of mk ends at e[l] - 1, so the bound over the whole level
-        // (the fence tree's layout is that of the whole level) is its start.
-        const uint32_t s = fenced_bound(lv.kv[l], lv.fence[l], lv.len[l], mk, false);
-        if (l == mi && (lv.kv[l][s] & 1u)) {
-          rk = mk;
-          rv = lv.val[l][s];
-          f = 1;
-          done = true;
-          break;
+    }
+    uint32_t at = 0u;
+    while (best != kNoKey) {
+      at = run_start(lv, level, cur[level * kQueryThreads] - 1u, best);
+      if ((as_global(lv.kv[level])[at] & 1u) != 0u) break;
+      const uint32_t gone = best;
+      best = kNoKey;
+      for (int l = 0; l < lv.count; ++l) {
+        uint32_t p = cur[l * kQueryThreads];
+        if (p == 0u) continue;
+        uint32_t key = lv.kv[l][p - 1u] >> 1;
+        if (key == gone) {
+          p = run_start(lv, l, p - 1u, gone);
+          cur[l * kQueryThreads] = p;
+          if (p == 0u) continue;
+          key = lv.kv[l][p - 1u] >> 1;
         }
-        e[l] = s;
-        ck[l] = s > 0u ? (lv.kv[l][s - 1u] >> 1) : kNoKey;
+        if (best == kNoKey || key > best) {
+          best = key;
+          level = l;
+        }
       }
-      if (done) break;
+    }
+    if (i < nq) {
+      const bool f = best != kNoKey;
+      out_key[i] = f ? best : 0u;
+      out_val[i] = f ? as_global(lv.val[level])[at] : 0u;
+      out_found[i] = f ? 1 : 0;
     }
   }
-  out_key[i] = rk;
-  out_val[i] = rv;
-  out_found[i] = f;
 }
 
 // ------------------------------------------------------------ cleanup
@@ -2693,14 +2877,20 @@ __global__ void k_zero_u64(uint64_t* p) { *p = 0ull; }
 
 inline unsigned grid_for(uint64_t n, uint64_t per) { return static_cast<unsigned>((n + per - 1) / per); }
 
+// lds: bytes of dynamic LDS.
+template <typename Kernel, typename... Args>
+hipError_t launch_lds(Kernel k, unsigned grid, unsigned block, unsigned lds, hipStream_t s,
+                      const KTimer* t, Args... args) {
+  if (t != nullptr && (t->start != nullptr || t->stop != nullptr))
+    hipExtLaunchKernelGGL(k, dim3(grid), dim3(block), lds, s, t->start, t->stop, 0, args...);
+  else
+    k<<<grid, block, lds, s>>>(args...);
+  return hipGetLastError();
+}
 template <typename Kernel, typename... Args>
 hipError_t launch(Kernel k, unsigned grid, unsigned block, hipStream_t s, const KTimer* t,
                   Args... args) {
-  if (t != nullptr && (t->start != nullptr || t->stop != nullptr))
-    hipExtLaunchKernelGGL(k, dim3(grid), dim3(block), 0, s, t->start, t->stop, 0, args...);
-  else
-    k<<<grid, block, 0, s>>>(args...);
-  return hipGetLastError();
+  return launch_lds(k, grid, block, 0, s, t, args...);
 }
 
 }  // namespace
@@ -2960,11 +3150,29 @@ hipError_t launch_fill_runs(uint32_t* a_kv, uint32_t* a_val, uint32_t* b_kv, uin
                 b_val, n);
 }
 
+// Tops and grid of a query kernel that strides over the queries.  Up to
+// kFewQueries the work-groups run side by side and loading the tops is part of
+// every query's latency, so only what one round of loads brings (64 queries on
+// five levels: 23.7 us with 2048 words, 30.1 with 8192); above, the grid is as
+// large as keeps the loading of the tops small beside the queries (with one
+// level 2^22 lookups take 212 us in 4096 work-groups, 222 in 1280).
+constexpr uint32_t kFewQueries = 1u << 16;
+constexpr uint32_t kTopWordsFew = 2048;
+static TopSet query_tops(const LevelSet& lv, uint32_t nq) {
+  return top_set(lv, nq <= kFewQueries ? kTopWordsFew : kTopWords);
+}
+static unsigned query_grid(const TopSet& ts, uint64_t nq) {
+  const uint64_t g = (nq + kQueryThreads - 1) / kQueryThreads;
+  const uint64_t most = 5u * 256u * (8192u / (ts.words > 2048u ? ts.words : 2048u));
+  return static_cast<unsigned>(g < most ? g : most);
+}
+
 hipError_t launch_lookup(const LevelSet& lv, const uint32_t* q, uint32_t nq, uint32_t* out_val,
                          uint8_t* out_found, hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  return launch(k_lookup, grid_for(nq, kQueryThreads), kQueryThreads, stream, t, lv, q, nq,
-                out_val, out_found);
+  const TopSet ts = query_tops(lv, nq);
+  return launch_lds(k_lookup, query_grid(ts, nq), kQueryThreads, ts.words * 4u, stream, t, lv, ts,
+                    q, nq, out_val, out_found);
 }
 
 hipError_t launch_count(const LevelSet& lv, const uint32_t* lo, const uint32_t* hi, uint32_t nq,
@@ -2973,8 +3181,9 @@ hipError_t launch_count(const LevelSet& lv, const uint32_t* lo, const uint32_t* 
   if (nq == 0) return hipSuccess;
   auto k = lv.count <= 1 ? k_count<1> : lv.count <= 8 ? k_count<8> : lv.count <= 16 ? k_count<16>
                                                                            : k_count<kMaxLevels>;
-  return launch(k, grid_for(nq, kQueryThreads), kQueryThreads, stream, t, lv, lo, hi, nq,
-                counts, scan_status, static_cast<uint64_t>(scan_words), bounds);
+  const TopSet ts = query_tops(lv, nq);
+  return launch_lds(k, query_grid(ts, nq), kQueryThreads, ts.words * 4u, stream, t, lv, ts, lo, hi, nq,
+                    counts, scan_status, static_cast<uint64_t>(scan_words), bounds);
 }
 
 size_t scan_status_words(uint32_t nq) { return 1 + grid_for(nq, kScanTile); }
@@ -2991,16 +3200,20 @@ hipError_t launch_successor(const LevelSet& lv, const uint32_t* q, uint32_t nq, 
                             uint32_t* out_val, uint8_t* out_found, hipStream_t stream,
                             const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  return launch(k_successor, grid_for(nq, kQueryThreads), kQueryThreads, stream, t, lv, q, nq,
-                out_key, out_val, out_found);
+  const TopSet ts = query_tops(lv, nq);
+  const unsigned lds = (ts.words + static_cast<unsigned>(lv.count) * kQueryThreads) * 4u;
+  return launch_lds(k_successor, query_grid(ts, nq), kQueryThreads, lds, stream, t, lv, ts, q, nq,
+                    out_key, out_val, out_found);
 }
 
 hipError_t launch_predecessor(const LevelSet& lv, const uint32_t* q, uint32_t nq,
                               uint32_t* out_key, uint32_t* out_val, uint8_t* out_found,
                               hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  return launch(k_predecessor, grid_for(nq, kQueryThreads), kQueryThreads, stream, t, lv, q, nq,
-                out_key, out_val, out_found);
+  const TopSet ts = query_tops(lv, nq);
+  const unsigned lds = (ts.words + static_cast<unsigned>(lv.count) * kQueryThreads) * 4u;
+  return launch_lds(k_predecessor, query_grid(ts, nq), kQueryThreads, lds, stream, t, lv, ts, q, nq,
+                    out_key, out_val, out_found);
 }
 
 uint32_t clean_tiles(uint32_t n) { return grid_for(n, kCleanTile); }
@@ -3031,20 +3244,23 @@ hipError_t launch_range_emit(const LevelSet& lv, const uint32_t* lo, const uint3
                              uint32_t* out_keys, uint32_t* out_vals, uint64_t cap,
                              hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
+  // Emission from stored bounds and emission that searches (no scratch) are
+  // separate instantiations, so that the first keeps a smaller register
+  // footprint and no LDS for the tops.
+  TopSet ts{};
+  if (bounds == nullptr) ts = query_tops(lv, nq);
+  const unsigned grid = grid_for(nq, kQueryThreads);
   if (lv.count <= 1)
-    return launch(bounds != nullptr ? k_range_emit_one<4, false> : k_range_emit_one<4, true>,
-                  grid_for(nq, kQueryThreads), kQueryThreads, stream, t, lv, lo, hi, nq, offsets,
-                  bounds, out_keys, out_vals, cap);
-  // Emission from stored cursors and emission that searches (no scratch)
-  // are separate instantiations, so that the first keeps a smaller register
-  // footprint.
+    return launch_lds(bounds != nullptr ? k_range_emit_one<4, false> : k_range_emit_one<4, true>,
+                      grid, kQueryThreads, ts.words * 4u, stream, t, lv, ts, lo, hi, nq, offsets,
+                      bounds, out_keys, out_vals, cap);
   auto k = bounds != nullptr
                ? (lv.count <= 8 ? k_range_emit<8, false> : lv.count <= 16 ? k_range_emit<16, false>
                                                                           : k_range_emit<kMaxLevels, false>)
                : (lv.count <= 8 ? k_range_emit<8, true> : lv.count <= 16 ? k_range_emit<16, true>
                                                                          : k_range_emit<kMaxLevels, true>);
-  return launch(k, grid_for(nq, kQueryThreads), kQueryThreads, stream, t, lv, lo, hi, nq, offsets,
-                bounds, out_keys, out_vals, cap);
+  return launch_lds(k, grid, kQueryThreads, ts.words * 4u, stream, t, lv, ts, lo, hi, nq, offsets,
+                    bounds, out_keys, out_vals, cap);
 }
 
 }  // namespace lsm
