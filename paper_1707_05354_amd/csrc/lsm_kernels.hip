@@ -244,16 +244,31 @@ __device__ __forceinline__ uint32_t octet_sum(uint32_t x) {
 constexpr uint32_t kTopEntries = 2048;
 constexpr uint32_t kTopWords = 4096;
 static_assert(kMaxLevels * 64 <= kTopWords, "32 levels of at most 32 entries always fit");
-struct TopSet {
-  uint32_t at[kMaxLevels];   // first LDS word of the level's part
-  uint32_t cnt[kMaxLevels];  // its entries
-  uint32_t off[kMaxLevels];  // where that tree level starts in the fence tree
-  uint32_t t[kMaxLevels];    // which tree level it is
-  uint32_t words;            // LDS words of all parts
+
+// The occupied levels as the query kernels take them, newest first: what a
+// search reads of a level stands together (one or two cache lines of the
+// kernel's arguments, which every launch reads afresh).
+struct QLevel {
+  const uint32_t* kv;
+  const uint32_t* val;
+  const uint32_t* fence;
+  uint32_t len;
+  uint32_t top_at;   // first LDS word of the level's top
+  uint32_t top_cnt;  // its entries
+  uint32_t top_off;  // where the tree level above which the search starts ends
+  uint32_t top_t;    // and which one it is
 };
-inline TopSet top_set(const LevelSet& lv, uint32_t words) {
-  TopSet s{};
-  for (uint64_t cap = kTopEntries;; cap /= 2) {
+struct QLevels {
+  int count;
+  uint32_t words;  // LDS words of all tops
+  QLevel v[kMaxLevels];
+};
+// words: the most LDS words for the tops; 0 for none (every search then starts
+// at the root).
+inline QLevels query_levels(const LevelSet& lv, uint32_t words) {
+  QLevels s{};
+  s.count = lv.count;
+  for (uint64_t cap = words == 0 ? 32 : kTopEntries;; cap /= 2) {
     s.words = 0;
     for (int l = 0; l < lv.count; ++l) {
       uint64_t off = 0, c = (static_cast<uint64_t>(lv.len[l]) + 31) / 32;
@@ -263,10 +278,20 @@ inline TopSet top_set(const LevelSet& lv, uint32_t words) {
         c = (c + 31) / 32;
         ++t;
       }
-      s.at[l] = s.words;
-      s.cnt[l] = static_cast<uint32_t>(c);
-      s.off[l] = static_cast<uint32_t>(off);
-      s.t[l] = t;
+      QLevel& q = s.v[l];
+      q.kv = lv.kv[l];
+      q.val = lv.val[l];
+      q.fence = lv.fence[l];
+      q.len = lv.len[l];
+      if (words == 0) {
+        q.top_off = static_cast<uint32_t>(off + fence_pad(c));
+        q.top_t = t + 1;
+        continue;
+      }
+      q.top_at = s.words;
+      q.top_cnt = static_cast<uint32_t>(c);
+      q.top_off = static_cast<uint32_t>(off);
+      q.top_t = t;
       s.words += (static_cast<uint32_t>(c) + 63u) & ~63u;
     }
     if (s.words <= words || cap <= 32) return s;
@@ -281,10 +306,10 @@ __device__ __forceinline__ uint32_t top_word(uint32_t i) { return i ^ ((i >> 6) 
 // Loads every part (all threads of the work-group; kN waves).  The blocks of
 // 64 words are dealt to the waves in turn, eight in flight.
 template <int kN>
-__device__ __forceinline__ void load_tops(const LevelSet& lv, const TopSet& ts, uint32_t* top) {
+__device__ __forceinline__ void load_tops(const QLevels& lv, uint32_t* top) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
-  const uint32_t blocks = ts.words >> 6;
+  const uint32_t blocks = lv.words >> 6;
   for (uint32_t b0 = wave; b0 < blocks; b0 += 8 * kN) {
     uint32_t v[8];
 #pragma unroll
@@ -293,9 +318,9 @@ __device__ __forceinline__ void load_tops(const LevelSet& lv, const TopSet& ts, 
       v[u] = 0u;
       if (blk < blocks) {
         int l = 0;
-        while (l + 1 < lv.count && ts.at[l + 1] <= blk * 64u) ++l;
-        const uint32_t i = blk * 64u - ts.at[l] + lane;
-        if (i < ts.cnt[l]) v[u] = lv.fence[l][ts.off[l] + i];
+        while (l + 1 < lv.count && lv.v[l + 1].top_at <= blk * 64u) ++l;
+        const uint32_t i = blk * 64u - lv.v[l].top_at + lane;
+        if (i < lv.v[l].top_cnt) v[u] = lv.v[l].fence[lv.v[l].top_off + i];
       }
     }
 #pragma unroll
@@ -303,8 +328,8 @@ __device__ __forceinline__ void load_tops(const LevelSet& lv, const TopSet& ts, 
       const uint32_t blk = b0 + u * kN;
       if (blk < blocks) {
         int l = 0;
-        while (l + 1 < lv.count && ts.at[l + 1] <= blk * 64u) ++l;
-        top[ts.at[l] + top_word(blk * 64u - ts.at[l] + lane)] = v[u];
+        while (l + 1 < lv.count && lv.v[l + 1].top_at <= blk * 64u) ++l;
+        top[lv.v[l].top_at + top_word(blk * 64u - lv.v[l].top_at + lane)] = v[u];
       }
     }
   }
@@ -352,25 +377,30 @@ __device__ __forceinline__ void octet_lanes(uint32_t x, uint32_t (&q)[8]) {
 // without a query pass any key and ignore the result).  With kFind, *hit
 // receives whether the element at the bound can hold key k: exactly, or true
 // when it stands in the next line (one time in 32).
-template <bool kUpper, bool kFind>
-__device__ __forceinline__ uint32_t octet_bound(const LevelSet& lv, const TopSet& ts,
+template <bool kTop, bool kUpper, bool kFind>
+__device__ __forceinline__ uint32_t octet_bound(const QLevels& lv,
                                                 const uint32_t* top, int l, uint32_t k,
                                                 const uint32_t (&kq)[8], bool* hit) {
   static_assert(!kUpper || !kFind, "the bound of a key that is looked for is the lower one");
   const uint32_t lane = lane_id(), sub = lane & 7u;
-  const uint32_t n = lv.len[l];
+  const uint32_t n = lv.v[l].len;
   if (n == 0) {
     if (kFind) *hit = false;
     return 0u;
   }
   uint32_t g[8];
-  octet_lanes(top_count<kUpper>(top + ts.at[l], ts.cnt[l], k), g);
-  const uint32_t* tree = lv.fence[l];
-  uint32_t off = ts.off[l];
+  if constexpr (kTop) {
+    octet_lanes(top_count<kUpper>(top + lv.v[l].top_at, lv.v[l].top_cnt, k), g);
+  } else {  // no tops: from the root, which is the first line of its tree level
+#pragma unroll
+    for (int j = 0; j < 8; ++j) g[j] = 1u;
+  }
+  const uint32_t* tree = lv.v[l].fence;
+  uint32_t off = lv.v[l].top_off;
   // A tree level's answer lies in the line that starts at its parent's entry
   // g - 1; the line's first entry qualifies with its parent, and with g = 0
   // no entry of line 0 qualifies, so a plain count serves both.
-  for (uint32_t t = ts.t[l] - 1; t >= 1; --t) {
+  for (uint32_t t = lv.v[l].top_t - 1; t >= 1; --t) {
     const uint32_t ct = static_cast<uint32_t>((static_cast<uint64_t>(n) + (1ull << (5 * t)) - 1) >> (5 * t));
     off -= static_cast<uint32_t>(fence_pad(ct));
     const uint32_t* line = tree + off + 4u * sub;
@@ -403,7 +433,7 @@ __device__ __forceinline__ uint32_t octet_bound(const LevelSet& lv, const TopSet
   }
   // The level's own line.  Key variables are compared whole: below 2 k, or at
   // most 2 k + 1.  (Keys from 2^31 on are above every element.)
-  const uint32_t* kv = lv.kv[l];
+  const uint32_t* kv = lv.v[l].kv;
   uint4 w[8];
   if ((n & 31u) == 0) {
 #pragma unroll
@@ -2095,12 +2125,13 @@ __global__ __launch_bounds__(kThreads) void k_fill_runs(uint32_t* a_kv, uint32_t
 // (1.39 ms with whole descents: then the addresser and the longer chain of
 // dependent loads bound it too); with one level 212 us (244).  Five waves a
 // SIMD hide the chain; at four (98 registers) ten levels take 1.10 ms.
-__global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(LevelSet lv, TopSet ts,
+template <bool kTop>
+__global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(QLevels lv,
                                                              const uint32_t* q, uint32_t nq,
                                                              uint32_t* out_val,
                                                              uint8_t* out_found) {
   extern __shared__ uint32_t top[];
-  load_tops<kQueryThreads / 64>(lv, ts, top);
+  if constexpr (kTop) load_tops<kQueryThreads / 64>(lv, top);
   for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
        q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
     // Every lane stays until the wave is done: the searches are wave-wide.
@@ -2115,9 +2146,9 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(LevelSet lv, TopSet
     for (int l = 0; l < lv.count; ++l) {
       if (ballot(!done) == 0) break;
       bool hit;
-      const uint32_t p = octet_bound<false, true>(lv, ts, top, l, k, kq, &hit);
-      if (!done && hit && p < lv.len[l]) {
-        const uint32_t x = lv.kv[l][p], y = lv.val[l][p];
+      const uint32_t p = octet_bound<kTop, false, true>(lv, top, l, k, kq, &hit);
+      if (!done && hit && p < lv.v[l].len) {
+        const uint32_t x = lv.v[l].kv[p], y = lv.v[l].val[p];
         if ((x >> 1) == k) {
           if (x & 1u) {
             v = y;
@@ -2134,7 +2165,8 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(LevelSet lv, TopSet
   }
 }
 
-constexpr uint32_t kNoKey = 0xFFFFFFFFu;  // above every original key (< 2^31)
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;   // above every original key (< 2^31)
+constexpr uint32_t kMaxKey = 0x7FFFFFFFu;  // largest encodable original key
 
 // First index in (c, e) whose original key differs from k, where kv[c] has
 // key k: one probe for the common run of length 1, then a galloping search,
@@ -2156,43 +2188,6 @@ __device__ __forceinline__ uint32_t skip_run(const uint32_t* kv, uint32_t c, uin
     else hi = mid;
   }
   return hi;
-}
-
-// The candidates of a query [k1, k2] in the first kW occupied levels run
-// from lower_bound(k1) (one fence-tree descent per level) up to the first
-// key above k2, which the walks find by reading on (they read every
-// candidate anyway), so no second descent is made.  The cursors are kept in
-// registers: level l's goes to slot l through a compare per slot, so no
-// register array is indexed at run time (which would put the walk state in
-// scratch memory).  A slot past the occupied levels stays at 0 of a level of
-// length 0 (lv.len is zero there).
-// The descents are wave-wide (octet_bound): every lane of the wave calls
-// this; for k1 > k2 the walks then find no candidate (every key from the
-// lower bound on is above k2).
-template <int kW>
-__device__ __forceinline__ void level_bounds(const LevelSet& lv, const TopSet& ts,
-                                             const uint32_t* top, uint32_t k1,
-                                             uint32_t (&cur)[kW]) {
-  uint32_t kq[8];
-  octet_lanes(k1, kq);
-#pragma unroll
-  for (int q = 0; q < kW; ++q) cur[q] = 0u;
-  for (int l = 0; l < lv.count && l < kW; ++l) {
-    const uint32_t lo = octet_bound<false, false>(lv, ts, top, l, k1, kq, nullptr);
-#pragma unroll
-    for (int q = 0; q < kW; ++q) {
-      if (q == l) cur[q] = lo;
-    }
-  }
-}
-
-// Key of the candidate at cur in a level, or kNoKey past the level's end or
-// past k2.
-__device__ __forceinline__ uint32_t cand_key(const uint32_t* kv, uint32_t cur, uint32_t end,
-                                             uint32_t k2) {
-  if (cur >= end) return kNoKey;
-  const uint32_t key = kv[cur] >> 1;
-  return key <= k2 ? key : kNoKey;
 }
 
 // One level: the live keys among the candidates of [k1, k2], from p =
@@ -2238,225 +2233,382 @@ __device__ __forceinline__ uint32_t count_run_starts(const uint32_t* kv, uint32_
   return count;
 }
 
-// Walk the candidates of all occupied levels in key order.  For each
-// distinct key the element met first is the newest instance (smaller levels
-// are newer, and inside a level a key's run starts with its newest
-// element); it counts when it is a regular element.  At most kW occupied
-// levels, the walk state in registers (loops unrolled over the kW slots).
-template <int kW>
-__device__ __forceinline__ uint32_t range_walk(const LevelSet& lv, uint32_t (&cur)[kW],
-                                               uint32_t k2) {
-  uint32_t ck[kW];
+constexpr int kQueryWaves = kQueryThreads / 64;
+
+// ---- Several levels.  The candidates of a query [k1, k2] in a level run from
+// lower_bound(k1) up to the first key above k2.  The eight lanes of an octet
+// work on one query: they read the next eight candidates of every level (16 of
+// the two largest) with the loads of all levels in flight together, and merge
+// what they have read in LDS.  2^20 ranges of 16 keys over ten levels are
+// counted in 533 us and emitted in 538, about 22 lines of memory a query each
+// (982 and 1003 us with one lane per query and one dependent load per
+// candidate); 2^15 ranges of 512 keys in 1.1 and 2.1 ms (2.0 and 30.9).
+//
+// A wave's LDS: the cursors of its 64 queries (level l of query i at word
+// 64 l + i), then one list of kv words (and, to emit, one of values) per octet.
+struct WalkLds {
+  uint32_t* cur;   // [levels][64]
+  uint32_t* list;  // this octet's list
+  uint32_t* vals;  // its values (emission only)
+};
+// List entries of an octet: a multiple of 4 words (16-byte reads), an odd one,
+// so that the octets' lists start on different LDS banks.
+__host__ __device__ inline uint32_t walk_list(uint32_t levels) {
+  const uint32_t quads = 2 * levels + 4;  // 8 entries a level, 16 of two
+  return 4u * (quads | 1u);
+}
+__host__ __device__ inline uint32_t walk_words(uint32_t levels, bool emit) {
+  return 64u * levels + 8u * walk_list(levels) * (emit ? 2u : 1u);
+}
+__device__ __forceinline__ WalkLds walk_lds(uint32_t* wave_lds, uint32_t levels, bool emit) {
+  const uint32_t octet = lane_id() >> 3, len = walk_list(levels);
+  WalkLds w;
+  w.cur = wave_lds;
+  w.list = wave_lds + 64u * levels + octet * len;
+  w.vals = emit ? w.list + 8u * len : nullptr;
+  return w;
+}
+
+// Orders a wave's LDS accesses before and after it for the compiler (the
+// hardware applies one wave's in issue order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The octet's bits of a wave ballot.
+__device__ __forceinline__ uint32_t octet_ballot(bool p) {
+  const uint64_t m = ballot(p);
+  return static_cast<uint32_t>(m >> (lane_id() & 56u)) & 0xFFu;
+}
+
+// One chunk of query `qi` of the wave (the same in all lanes of an octet, as h2
+// and live): fills the octet's list with every element of every level from its
+// cursor on whose key is at most k2 (kv word <= h2) and below the bound that
+// makes the chunk complete, in level order (newest first), each level's in its
+// own order, and moves the cursors past them.  The bound is the smallest last
+// key among the levels that may hold more; *bound receives it (kNoKey: the
+// query ends with this chunk).  Returns the list's length.  The two largest
+// levels (16 elements each) are held in registers, the others pass through the
+// list, eight levels' loads in flight, and are packed there in place.
+template <bool kEmit>
+__device__ __forceinline__ uint32_t walk_chunk(const QLevels& lv, const WalkLds& w, uint32_t qi,
+                                               uint32_t h2, bool live, uint32_t* bound) {
+  constexpr int kB = 8;
+  const uint32_t sub = lane_id() & 7u;
+  const int small = lv.count - 2;  // levels read eight at a time
+  uint32_t xw[4], aw[4], in = 0u;  // elements 8 (y & 1) .. of level small + y / 2
 #pragma unroll
-  for (int l = 0; l < kW; ++l) ck[l] = cand_key(lv.kv[l], cur[l], lv.len[l], k2);
-  uint32_t count = 0;
-  for (;;) {
-    uint32_t mk = kNoKey;
+  for (int y = 0; y < 4; ++y) {
+    const int l = small + y / 2;
+    aw[y] = w.cur[l * 64 + qi] + 8u * (y & 1) + sub;
+    const bool ok = live && aw[y] < lv.v[l].len;
+    xw[y] = ok ? lv.v[l].kv[aw[y]] : ~0u;
+    in |= ok ? 1u << y : 0u;
+  }
+  wave_sync();  // the previous chunk's list has been read
+  uint32_t B = kNoKey;
+  for (int l0 = 0; l0 < small; l0 += kB) {
+    uint32_t x[kB];
+    bool ok[kB];
 #pragma unroll
-    for (int l = 0; l < kW; ++l) mk = ck[l] < mk ? ck[l] : mk;
-    if (mk == kNoKey) break;
-    bool newest = true;
+    for (int u = 0; u < kB; ++u) {
+      const int l = l0 + u < small ? l0 + u : small;
+      const uint32_t at = w.cur[l * 64 + qi] + sub;
+      ok[u] = live && l < small && at < lv.v[l].len;
+      x[u] = ok[u] ? lv.v[l].kv[at] : ~0u;
+    }
 #pragma unroll
-    for (int l = 0; l < kW; ++l) {
-      if (ck[l] == mk) {
-        const uint32_t* kv = lv.kv[l];
-        if (newest) count += kv[cur[l]] & 1u;
-        newest = false;
-        cur[l] = skip_run(kv, cur[l], lv.len[l], mk);
-        ck[l] = cand_key(kv, cur[l], lv.len[l], k2);
+    for (int u = 0; u < kB; ++u) {
+      if (l0 + u < small) {
+        const uint32_t last = octet_lane<7>(ok[u] && x[u] <= h2 ? x[u] >> 1 : kNoKey);
+        B = last < B ? last : B;
+        w.list[(l0 + u) * 8 + sub] = x[u];
       }
     }
   }
-  return count;
+#pragma unroll
+  for (int y = 0; y < 4; ++y) {
+    const bool c = ((in >> y) & 1u) != 0u && xw[y] <= h2;
+    in = c ? in : in & ~(1u << y);
+    if (y & 1) {
+      const uint32_t last = octet_lane<7>(c ? xw[y] >> 1 : kNoKey);
+      B = last < B ? last : B;
+    }
+  }
+  // What is in is a prefix of the lanes (a level's keys ascend).
+  uint32_t vw[4];
+#pragma unroll
+  for (int y = 0; y < 4; ++y) {
+    in = (xw[y] >> 1) < B ? in : in & ~(1u << y);
+    vw[y] = kEmit && ((in >> y) & 1u) != 0u ? lv.v[small + y / 2].val[aw[y]] : 0u;
+  }
+  uint32_t n = 0;
+  auto put = [&](uint32_t x, uint32_t v, bool mine) {
+    if (mine) {
+      w.list[n + sub] = x;
+      if (kEmit) w.vals[n + sub] = v;
+    }
+    n += __popc(octet_ballot(mine));
+  };
+  for (int l0 = 0; l0 < small; l0 += kB) {
+    uint32_t x[kB], v[kB], at[kB];
+    bool mine[kB];
+#pragma unroll
+    for (int u = 0; u < kB; ++u) {
+      const int l = l0 + u < small ? l0 + u : small;
+      at[u] = w.cur[l * 64 + qi] + sub;
+      x[u] = w.list[(l < small ? l : 0) * 8 + sub];
+      mine[u] = live && l < small && at[u] < lv.v[l].len && x[u] <= h2 && (x[u] >> 1) < B;
+      v[u] = kEmit && mine[u] ? lv.v[l].val[at[u]] : 0u;
+    }
+    wave_sync();
+#pragma unroll
+    for (int u = 0; u < kB; ++u) {
+      if (l0 + u < small) {
+        const uint32_t n0 = n;
+        put(x[u], v[u], mine[u]);
+        w.cur[(l0 + u) * 64 + qi] = at[u] - sub + (n - n0);  // all eight lanes, the same
+      }
+    }
+  }
+#pragma unroll
+  for (int y = 0; y < 4; y += 2) {
+    const uint32_t n0 = n;
+    put(xw[y], vw[y], ((in >> y) & 1u) != 0u);
+    put(xw[y + 1], vw[y + 1], ((in >> (y + 1)) & 1u) != 0u);
+    w.cur[(small + y / 2) * 64 + qi] = aw[y] - sub + (n - n0);
+  }
+  // The last quad is filled up with words above every valid one.
+  if (n + sub < ((n + 3u) & ~3u)) w.list[n + sub] = ~0u;
+  wave_sync();
+  *bound = B;
+  return n;
 }
 
-// Count pass.  With one level and bounds non-null, each query's candidate
-// bounds [lower_bound(lo), upper_bound(hi)) are also stored (two words per
-// query) for the emission pass.
-template <int kW>
-__global__ __launch_bounds__(kQueryThreads) void k_count(LevelSet lv, TopSet ts,
+// Whether list entry i is its key's newest instance in the list and regular.
+__device__ __forceinline__ bool list_valid(const uint32_t* list, uint32_t i, uint32_t x) {
+  uint32_t near = ~0u;  // zero when an earlier entry has x's key
+  const uint4* q = reinterpret_cast<const uint4*>(list);
+  for (uint32_t e = 0; e < i; e += 4) {
+    const uint4 y = q[e >> 2];
+    const uint32_t y4[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+      const uint32_t d = (y4[r] ^ x) >> 1;
+      near = (e + r < i && d < near) ? d : near;
+    }
+  }
+  return near != 0u && (x & 1u) != 0u;
+}
+
+// A chunk that holds nothing below its bound B starts with a run of key B that
+// fills what was read of some level.  Finds B's newest instance (*x, and its
+// value with kEmit) and moves every cursor past its run.
+template <bool kEmit>
+__device__ __forceinline__ void walk_run(const QLevels& lv, const WalkLds& w, uint32_t qi,
+                                         uint32_t B, uint32_t* x, uint32_t* v) {
+  bool found = false;
+  for (int l = 0; l < lv.count; ++l) {
+    const uint32_t p = w.cur[l * 64 + qi], n = lv.v[l].len;
+    const uint32_t y = p < n ? lv.v[l].kv[p] : 0u;
+    if (p >= n || (y >> 1) != B) continue;
+    if (!found) {
+      found = true;
+      *x = y;
+      if (kEmit) *v = lv.v[l].val[p];
+    }
+    w.cur[l * 64 + qi] = skip_run(lv.v[l].kv, p, n, B);  // all eight lanes, the same
+  }
+}
+
+// An octet takes `per` queries (1, 2, 4 or 8): the query of a lane, counted from
+// the work-group's first.  With fewer than eight, lanes per .. 7 search along
+// with their octet's queries again and keep nothing.
+__device__ __forceinline__ uint32_t query_slot(uint32_t per) {
+  return (threadIdx.x >> 3) * per + (threadIdx.x & (per - 1u));
+}
+
+// Count pass.  With bounds non-null, each query's position in the levels is
+// stored for the emission pass: with one level its candidate bounds
+// [lower_bound(lo), upper_bound(hi)) (two words per query), with several its
+// cursors (lower bounds), level-major (word l * nq + query).
+// kMany: several occupied levels.
+template <bool kTop, bool kMany>
+__global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
                                                          const uint32_t* lo, const uint32_t* hi,
-                                                         uint32_t nq, uint32_t* counts,
-                                                         uint64_t* scan_status,
+                                                         uint32_t nq, uint32_t per,
+                                                         uint32_t* counts, uint64_t* scan_status,
                                                          uint64_t scan_words, uint32_t* bounds) {
   extern __shared__ uint32_t top[];
-  const uint64_t threads = static_cast<uint64_t>(gridDim.x) * kQueryThreads;
-  const uint64_t g0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads;
   if (scan_status != nullptr)
-    for (uint64_t w = g0 + threadIdx.x; w < scan_words; w += threads) scan_status[w] = 0ull;
-  load_tops<kQueryThreads / 64>(lv, ts, top);
-  for (uint64_t q0 = g0; q0 < nq; q0 += threads) {
+    for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * kQueryThreads + threadIdx.x;
+         w < scan_words; w += static_cast<uint64_t>(gridDim.x) * kQueryThreads)
+      scan_status[w] = 0ull;
+  if constexpr (kTop) load_tops<kQueryWaves>(lv, top);
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & 7u;
+  const uint32_t L = static_cast<uint32_t>(lv.count);
+  WalkLds w{};
+  if (kMany) w = walk_lds(top + lv.words + wave * walk_words(L, false), L, false);
+  const uint32_t block = kQueryThreads / 8 * per, slot = query_slot(per);
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * block; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * block) {
     // Every lane takes part in the wave-wide descents; lanes without a query
-    // search the empty range [1, 0].  Several levels: with bounds non-null,
-    // each query's per-level cursors (lower bounds) are stored level-major
-    // (word l * nq + query) for the emission pass.
-    const uint64_t gi = q0 + threadIdx.x;
-    const bool active = gi < nq;
-    const uint32_t k1 = active ? lo[gi] : 1u, k2 = active ? hi[gi] : 0u;
-    if constexpr (kW == 1) {
+    // search the empty range [1, 0].
+    const uint64_t gi = q0 + slot;
+    const bool active = sub < per && gi < nq;
+    const uint32_t k1 = gi < nq ? lo[gi] : 1u, k2 = gi < nq ? hi[gi] : 0u;
+    uint32_t kq[8];
+    octet_lanes(k1, kq);
+    if constexpr (!kMany) {
       // Both bounds by descents, so the scan reads only the candidates.
-      uint32_t kq[8];
-      octet_lanes(k1, kq);
-      uint32_t p = octet_bound<false, false>(lv, ts, top, 0, k1, kq, nullptr);
+      uint32_t p = octet_bound<kTop, false, false>(lv, top, 0, k1, kq, nullptr);
       octet_lanes(k2, kq);
-      uint32_t e = octet_bound<true, false>(lv, ts, top, 0, k2, kq, nullptr);
+      uint32_t e = octet_bound<kTop, true, false>(lv, top, 0, k2, kq, nullptr);
       if (!active) continue;
       uint32_t c = 0;
-      if (k1 <= k2) c = count_run_starts(lv.kv[0], p, e, k2, &e);
+      if (k1 <= k2) c = count_run_starts(lv.v[0].kv, p, e, k2, &e);
       else p = e = 0;
       if (bounds != nullptr) reinterpret_cast<uint2*>(bounds)[gi] = make_uint2(p, e);
       counts[gi] = c;
     } else {
-      uint32_t cur[kW];
-      level_bounds<kW>(lv, ts, top, k1, cur);
-      if (bounds != nullptr && active) {
-#pragma unroll
-        for (int q = 0; q < kW; ++q)
-          if (q < lv.count) bounds[static_cast<size_t>(q) * nq + gi] = cur[q];
+      for (uint32_t l = 0; l < L; ++l) {
+        const uint32_t p =
+            octet_bound<kTop, false, false>(lv, top, static_cast<int>(l), k1, kq, nullptr);
+        w.cur[l * 64 + lane] = p;
+        if (bounds != nullptr && active) bounds[static_cast<size_t>(l) * nq + gi] = p;
       }
-      const uint32_t c = range_walk<kW>(lv, cur, k2);
-      if (active) counts[gi] = c;
+      wave_sync();
+      const uint32_t h2 = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
+      uint32_t res = 0;
+      for (uint32_t r = 0; r < per; ++r) {
+        const uint32_t qi = (lane & 56u) + r;
+        const uint32_t h =
+            static_cast<uint32_t>(__shfl(static_cast<int>(h2), static_cast<int>(qi), 64));
+        uint32_t c = 0;  // this lane's share of the count
+        bool live = true;
+        while (ballot(live) != 0) {
+          uint32_t B;
+          const uint32_t n = walk_chunk<false>(lv, w, qi, h, live, &B);
+          for (uint32_t i = sub; i < n; i += 8) c += list_valid(w.list, i, w.list[i]) ? 1u : 0u;
+          if (live && B != kNoKey && n == 0) {
+            uint32_t x = 0u, v = 0u;
+            walk_run<false>(lv, w, qi, B, &x, &v);
+            if (sub == 0) c += x & 1u;
+          }
+          live = live && B != kNoKey;
+        }
+        c = octet_sum(c);
+        res = sub == r ? c : res;
+      }
+      if (active) counts[gi] = res;
     }
   }
 }
 
-// Resumable form of the several-level range_walk for the emission pass:
-// the walk of one query keeps its cursors between calls, and each call
-// emits the pairs whose output positions fall in [pos, lim), writing pair
-// position x at sk[x - c0] / sv[x - c0].  Returns the next position.  The
-// pairs and their order are range_walk's.
-template <int kW>
-struct WalkMany {
-  uint32_t cur[kW], ck[kW];
-  uint32_t k2;
-};
-
-// The cursors come from the count pass (cursors non-null: word l * nq + i
-// for query i, read only when `use`) or from wave-wide descents (every lane
-// of the wave calls it then).
-template <int kW, bool kSearch>
-__device__ __forceinline__ void walk_init(const LevelSet& lv, const TopSet& ts,
-                                          const uint32_t* top, uint32_t k1, uint32_t k2,
-                                          const uint32_t* cursors, uint32_t nq, uint32_t i,
-                                          bool use, WalkMany<kW>& w) {
-  w.k2 = k2;
-  if constexpr (!kSearch) {
-#pragma unroll
-    for (int q = 0; q < kW; ++q)
-      w.cur[q] = (use && q < lv.count) ? cursors[static_cast<size_t>(q) * nq + i] : 0u;
-  } else {
-    level_bounds<kW>(lv, ts, top, k1, w.cur);
-  }
-#pragma unroll
-  for (int l = 0; l < kW; ++l) w.ck[l] = cand_key(lv.kv[l], w.cur[l], lv.len[l], k2);
-}
-
-// Several levels: the k-way walk over the level runs in key order; the
-// element met first for each key (smallest level first) is its newest
-// instance, emitted when regular.
-template <int kW>
-__device__ __forceinline__ uint64_t walk_emit(const LevelSet& lv, WalkMany<kW>& w, uint64_t pos,
-                                              uint64_t lim, uint64_t c0, uint32_t* sk,
-                                              uint32_t* sv) {
-  for (;;) {
-    uint32_t mk = kNoKey;
-#pragma unroll
-    for (int l = 0; l < kW; ++l) mk = w.ck[l] < mk ? w.ck[l] : mk;
-    if (mk == kNoKey) break;
-    // The newest instance: the first level holding the key.
-    uint32_t x = 0, v = 0;
-    bool newest = true;
-#pragma unroll
-    for (int l = 0; l < kW; ++l) {
-      if (newest && w.ck[l] == mk) {
-        x = lv.kv[l][w.cur[l]];
-        v = lv.val[l][w.cur[l]];
-        newest = false;
-      }
-    }
-    if (x & 1u) {
-      if (pos >= lim) break;  // this key is emitted by a later call
-      sk[pos - c0] = mk;
-      sv[pos - c0] = v;
-      ++pos;
-    }
-#pragma unroll
-    for (int l = 0; l < kW; ++l) {
-      if (w.ck[l] == mk) {
-        w.cur[l] = skip_run(lv.kv[l], w.cur[l], lv.len[l], mk);
-        w.ck[l] = cand_key(lv.kv[l], w.cur[l], lv.len[l], w.k2);
-      }
-    }
-  }
-  return pos;
-}
-
-// Stage 3 of sec. IV-C / IV-D over several levels, with coalesced writes.
-// The pairs of a wave's 64 consecutive queries form one contiguous span of
-// the output, which the wave produces in chunks of kEmitChunk pairs: every query emits the pairs
-// that fall in the chunk into the wave's LDS buffer (its walk resumes where
-// the previous chunk stopped it), then the wave copies the chunk out with
-// consecutive lanes on consecutive addresses.  A query whose pairs would end
-// beyond cap writes nothing (the caller sees offsets[q + 1] > cap); the other
-// checks only guard against offsets corrupted by a timed-out scan.
-constexpr uint32_t kEmitChunk = 512;
-constexpr int kQueryWaves = kQueryThreads / 64;
-
-template <int kW, bool kSearch>
-__global__ __launch_bounds__(kQueryThreads) void k_range_emit(LevelSet lv, TopSet ts,
+// Stage 3 of sec. IV-C / IV-D over several levels.  An octet writes its
+// query's pairs at the query's offset, chunk by chunk: a valid entry's place is
+// the number of valid entries of the chunk with a smaller key.  A query whose
+// pairs would end beyond cap writes nothing (the caller sees
+// offsets[q + 1] > cap); writes stay inside [offsets[q], offsets[q + 1]) even
+// for offsets corrupted by a timed-out scan.  Cursors as the count pass stored
+// them, or, with kSearch, from descents.
+template <bool kTop, bool kSearch>
+__global__ __launch_bounds__(kQueryThreads) void k_range_emit(QLevels lv,
                                                               const uint32_t* lo,
                                                               const uint32_t* hi, uint32_t nq,
+                                                              uint32_t per,
                                                               const uint64_t* offsets,
                                                               const uint32_t* cursors,
                                                               uint32_t* out_keys,
                                                               uint32_t* out_vals, uint64_t cap) {
-  __shared__ uint32_t sk[kQueryWaves][kEmitChunk], sv[kQueryWaves][kEmitChunk];
-  __shared__ uint32_t s_rounds[kQueryWaves];
   extern __shared__ uint32_t top[];
-  if (kSearch) load_tops<kQueryWaves>(lv, ts, top);
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t i = blockIdx.x * kQueryThreads + tid;
-  const uint32_t q0 = blockIdx.x * kQueryThreads + wave * 64;
-  const uint32_t qa = q0 < nq ? q0 : nq, qb = q0 + 64 < nq ? q0 + 64 : nq;
-  const uint64_t base = offsets[qa], span_end = offsets[qb], all = offsets[nq];
-  const bool active = i < nq;
-  const uint64_t o = active ? offsets[i] : 0, e = active ? offsets[i + 1] : 0;
-  const bool fits = active && e >= o && o >= base && e <= span_end && e <= all && e <= cap;
-  // The writable part of the span ends where the first query that does not
-  // fit begins (offsets are non-decreasing).
-  uint64_t stop = (active && !fits) ? o : ~0ull;
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) {
-    const uint64_t y = __shfl_xor(stop, d, 64);
-    stop = y < stop ? y : stop;
-  }
-  const uint64_t copy_end = stop < span_end ? stop : span_end;
-  const uint32_t rounds =
-      copy_end > base ? static_cast<uint32_t>((copy_end - base + kEmitChunk - 1) / kEmitChunk) : 0u;
-  if (lane == 0) s_rounds[wave] = rounds;
-  static_assert(kW > 1, "one level: k_range_emit_one");
-  WalkMany<kW> w;
-  // Stored cursors (only the queries that emit read theirs), or wave-wide
-  // descents by every lane.
-  walk_init<kW, kSearch>(lv, ts, top, fits ? lo[i] : 1u, fits ? hi[i] : 0u, cursors, nq, i, fits, w);
-  __syncthreads();
-  uint32_t R = 0;
-#pragma unroll
-  for (int x = 0; x < kQueryWaves; ++x) R = s_rounds[x] > R ? s_rounds[x] : R;
-  uint64_t pos = o;
-  for (uint32_t r = 0; r < R; ++r) {
-    const uint64_t c0 = base + static_cast<uint64_t>(r) * kEmitChunk;
-    const uint64_t c1 = c0 + kEmitChunk;
-    if (fits && pos < e && pos < c1) pos = walk_emit(lv, w, pos, e < c1 ? e : c1, c0, sk[wave], sv[wave]);
-    __syncthreads();
-    for (uint32_t x = lane; x < kEmitChunk; x += 64) {
-      const uint64_t g = c0 + x;
-      if (g < copy_end) {
-        out_keys[g] = sk[wave][x];
-        out_vals[g] = sv[wave][x];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & 7u;
+  const uint32_t L = static_cast<uint32_t>(lv.count);
+  const WalkLds w = walk_lds(top + lv.words + wave * walk_words(L, true), L, true);
+  if constexpr (kSearch && kTop) load_tops<kQueryWaves>(lv, top);
+  const uint64_t all = offsets[nq];
+  const uint32_t block = kQueryThreads / 8 * per, slot = query_slot(per);
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * block; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * block) {
+    const uint64_t gi = q0 + slot;
+    uint64_t o = 0, z = 0;
+    if (gi < nq) {
+      o = offsets[gi];
+      z = offsets[gi + 1];
+    }
+    const bool emit = z > o && z <= all && z <= cap;
+    if (!emit) z = o;
+    const uint32_t k1 = emit ? lo[gi] : 1u, k2 = emit ? hi[gi] : 0u;
+    if constexpr (kSearch) {
+      uint32_t kq[8];
+      octet_lanes(k1, kq);
+      for (uint32_t l = 0; l < L; ++l)
+        w.cur[l * 64 + lane] =
+            octet_bound<kTop, false, false>(lv, top, static_cast<int>(l), k1, kq, nullptr);
+    } else {
+      if (emit)
+        for (uint32_t l = 0; l < L; ++l)
+          w.cur[l * 64 + lane] = cursors[static_cast<size_t>(l) * nq + gi];
+    }
+    wave_sync();
+    const uint32_t h2 = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
+    for (uint32_t r = 0; r < per; ++r) {
+      const int qi = static_cast<int>((lane & 56u) + r);
+      const uint32_t h = static_cast<uint32_t>(__shfl(static_cast<int>(h2), qi, 64));
+      uint64_t at = __shfl(o, qi, 64);
+      const uint64_t end = __shfl(z, qi, 64);
+      bool live = at < end;
+      while (ballot(live) != 0) {
+        uint32_t B;
+        const uint32_t n = walk_chunk<true>(lv, w, static_cast<uint32_t>(qi), h, live, &B);
+        // Mark what is not valid, from the last entries down (an entry is
+        // compared with those before it), then rank the rest.
+        uint64_t mine = 0;  // this lane's valid entries, bit i / 8
+        uint32_t total = 0;
+        for (uint32_t i0 = n & ~7u;; i0 -= 8) {
+          const uint32_t i = i0 + sub;
+          const uint32_t x = i < n ? w.list[i] : 0u;
+          const bool ok = i < n && list_valid(w.list, i, x);
+          mine |= ok ? 1ull << (i0 >> 3) : 0ull;
+          total += __popc(octet_ballot(ok));
+          wave_sync();
+          if (i < n && !ok) w.list[i] = ~0u;
+          if (i0 == 0) break;
+        }
+        wave_sync();
+        const uint4* q4 = reinterpret_cast<const uint4*>(w.list);
+        for (uint32_t i = sub; i < n; i += 8) {
+          if (((mine >> (i >> 3)) & 1ull) == 0) continue;
+          const uint32_t x = w.list[i];
+          uint32_t rank = 0;
+          for (uint32_t e = 0; e < n; e += 4) {
+            const uint4 y = q4[e >> 2];
+            rank += (y.x < x ? 1u : 0u) + (y.y < x ? 1u : 0u) + (y.z < x ? 1u : 0u) +
+                    (y.w < x ? 1u : 0u);
+          }
+          if (at + rank < end) {
+            out_keys[at + rank] = x >> 1;
+            out_vals[at + rank] = w.vals[i];
+          }
+        }
+        at += total;
+        if (live && B != kNoKey && n == 0) {
+          uint32_t x = 0u, v = 0u;
+          walk_run<true>(lv, w, static_cast<uint32_t>(qi), B, &x, &v);
+          if ((x & 1u) != 0u && at < end) {
+            if (sub == 0) {
+              out_keys[at] = B;
+              out_vals[at] = v;
+            }
+            ++at;
+          }
+        }
+        live = live && B != kNoKey && at < end;
       }
     }
-    __syncthreads();
+    wave_sync();  // the cursors have been read
   }
 }
 
@@ -2510,15 +2662,15 @@ __device__ __forceinline__ void emit_run_starts(const uint32_t* kv, const uint32
 // whose pairs would end beyond cap writes nothing (the caller sees
 // offsets[q + 1] > cap); writes stay inside [offsets[q], offsets[q + 1])
 // even for offsets corrupted by a timed-out scan.
-template <int kU, bool kSearch>
+template <bool kTop, int kU, bool kSearch>
 __global__ __launch_bounds__(kQueryThreads) void k_range_emit_one(
-    LevelSet lv, TopSet ts, const uint32_t* lo, const uint32_t* hi, uint32_t nq, const uint64_t* offsets,
+    QLevels lv, const uint32_t* lo, const uint32_t* hi, uint32_t nq, const uint64_t* offsets,
     const uint32_t* bounds, uint32_t* out_keys, uint32_t* out_vals, uint64_t cap) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t i = blockIdx.x * kQueryThreads + threadIdx.x;
-  const uint32_t* kv = lv.kv[0];
-  const uint32_t* vv = lv.val[0];
-  const uint32_t len = lv.len[0];
+  const uint32_t* kv = lv.v[0].kv;
+  const uint32_t* vv = lv.v[0].val;
+  const uint32_t len = lv.v[0].len;
   uint32_t p = 0, e = 0;
   uint64_t o = 0, z = 0;
   bool emit = false;
@@ -2540,13 +2692,13 @@ __global__ __launch_bounds__(kQueryThreads) void k_range_emit_one(
     // Wave-wide descents: every lane searches (an empty range if it emits
     // nothing).
     extern __shared__ uint32_t top[];
-    load_tops<kQueryThreads / 64>(lv, ts, top);
+    if constexpr (kTop) load_tops<kQueryThreads / 64>(lv, top);
     const uint32_t k1 = emit ? lo[i] : 1u, k2 = emit ? hi[i] : 0u;
     uint32_t kq[8];
     octet_lanes(k1, kq);
-    p = octet_bound<false, false>(lv, ts, top, 0, k1, kq, nullptr);
+    p = octet_bound<kTop, false, false>(lv, top, 0, k1, kq, nullptr);
     octet_lanes(k2, kq);
-    e = octet_bound<true, false>(lv, ts, top, 0, k2, kq, nullptr);
+    e = octet_bound<kTop, true, false>(lv, top, 0, k2, kq, nullptr);
     if (!emit || k1 > k2) p = e = 0;
   }
   e = e < len ? e : len;
@@ -2654,8 +2806,6 @@ __global__ __launch_bounds__(kThreads) void k_scan(const uint32_t* counts, uint3
 }
 
 // ------------------------------------------------------------ order queries
-constexpr uint32_t kMaxKey = 0x7FFFFFFFu;  // largest encodable original key
-
 // Successor: the smallest key at the levels' upper bounds of q.  Its newest
 // instance is the one of the first level that holds it; nearly always a
 // regular element, and the answer.  A tombstone drops the key: every level
@@ -2663,14 +2813,15 @@ constexpr uint32_t kMaxKey = 0x7FFFFFFFu;  // largest encodable original key
 // stand in LDS (word l * kQueryThreads + thread), since an array indexed by
 // the level takes 148 registers: three waves a SIMD, 439 us for 2^20 queries
 // on seven levels; descending again from the dropped key takes 547.
-__global__ __launch_bounds__(kQueryThreads, 5) void k_successor(LevelSet lv, TopSet ts,
+template <bool kTop>
+__global__ __launch_bounds__(kQueryThreads, 5) void k_successor(QLevels lv,
                                                                 const uint32_t* q, uint32_t nq,
                                                                 uint32_t* out_key,
                                                                 uint32_t* out_val,
                                                                 uint8_t* out_found) {
   extern __shared__ uint32_t top[];
-  uint32_t* cur = top + ts.words + threadIdx.x;
-  load_tops<kQueryThreads / 64>(lv, ts, top);
+  uint32_t* cur = top + lv.words + threadIdx.x;
+  if constexpr (kTop) load_tops<kQueryThreads / 64>(lv, top);
   for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
        q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
     const uint64_t i = q0 + threadIdx.x;
@@ -2680,10 +2831,10 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_successor(LevelSet lv, Top
     uint32_t best = kNoKey, x = 0u;  // the smallest key and its newest instance
     int level = 0;
     for (int l = 0; l < lv.count; ++l) {
-      const uint32_t p = octet_bound<true, false>(lv, ts, top, l, k, kq, nullptr);
+      const uint32_t p = octet_bound<kTop, true, false>(lv, top, l, k, kq, nullptr);
       cur[l * kQueryThreads] = p;
-      if (p < lv.len[l]) {
-        const uint32_t y = lv.kv[l][p];
+      if (p < lv.v[l].len) {
+        const uint32_t y = lv.v[l].kv[p];
         if ((y >> 1) < best) {  // ties: the newer level's stays
           best = y >> 1;
           x = y;
@@ -2696,14 +2847,14 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_successor(LevelSet lv, Top
       const uint32_t gone = best;
       best = kNoKey;
       for (int l = 0; l < lv.count; ++l) {
-        const uint32_t* kv = lv.kv[l];
+        const uint32_t* kv = lv.v[l].kv;
         uint32_t p = cur[l * kQueryThreads];
-        if (p >= lv.len[l]) continue;
+        if (p >= lv.v[l].len) continue;
         uint32_t y = kv[p];
         if ((y >> 1) == gone) {
-          p = skip_run(kv, p, lv.len[l], gone);
+          p = skip_run(kv, p, lv.v[l].len, gone);
           cur[l * kQueryThreads] = p;
-          if (p >= lv.len[l]) continue;
+          if (p >= lv.v[l].len) continue;
           y = kv[p];
         }
         if ((y >> 1) < best) {
@@ -2716,29 +2867,30 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_successor(LevelSet lv, Top
     if (i < nq) {
       const bool f = best != kNoKey;
       out_key[i] = f ? best : 0u;
-      out_val[i] = f ? as_global(lv.val[level])[cur[level * kQueryThreads]] : 0u;
+      out_val[i] = f ? as_global(lv.v[level].val)[cur[level * kQueryThreads]] : 0u;
       out_found[i] = f ? 1 : 0;
     }
   }
 }
 
 // First element of the run of kv[c]'s key: nearly always c itself.
-__device__ __forceinline__ uint32_t run_start(const LevelSet& lv, int l, uint32_t c, uint32_t key) {
-  if (c == 0u || (as_global(lv.kv[l])[c - 1u] >> 1) != key) return c;
-  return fenced_bound(lv.kv[l], lv.fence[l], lv.len[l], key, false);
+__device__ __forceinline__ uint32_t run_start(const QLevels& lv, int l, uint32_t c, uint32_t key) {
+  if (c == 0u || (as_global(lv.v[l].kv)[c - 1u] >> 1) != key) return c;
+  return fenced_bound(lv.v[l].kv, lv.v[l].fence, lv.v[l].len, key, false);
 }
 
 // Predecessor: the mirror walk, the largest key below the levels' lower bounds
 // of q; the newest instance is the first element of its run in the first level
 // that holds it.
-__global__ __launch_bounds__(kQueryThreads, 5) void k_predecessor(LevelSet lv, TopSet ts,
+template <bool kTop>
+__global__ __launch_bounds__(kQueryThreads, 5) void k_predecessor(QLevels lv,
                                                                   const uint32_t* q, uint32_t nq,
                                                                   uint32_t* out_key,
                                                                   uint32_t* out_val,
                                                                   uint8_t* out_found) {
   extern __shared__ uint32_t top[];
-  uint32_t* cur = top + ts.words + threadIdx.x;  // the candidate is the element below
-  load_tops<kQueryThreads / 64>(lv, ts, top);
+  uint32_t* cur = top + lv.words + threadIdx.x;  // the candidate is the element below
+  if constexpr (kTop) load_tops<kQueryThreads / 64>(lv, top);
   for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
        q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
     const uint64_t i = q0 + threadIdx.x;
@@ -2748,10 +2900,10 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_predecessor(LevelSet lv, T
     uint32_t best = kNoKey;  // the largest key, kNoKey for none
     int level = 0;
     for (int l = 0; l < lv.count; ++l) {
-      const uint32_t p = octet_bound<false, false>(lv, ts, top, l, k, kq, nullptr);
+      const uint32_t p = octet_bound<kTop, false, false>(lv, top, l, k, kq, nullptr);
       cur[l * kQueryThreads] = p;
       if (p > 0u) {
-        const uint32_t key = lv.kv[l][p - 1u] >> 1;
+        const uint32_t key = lv.v[l].kv[p - 1u] >> 1;
         if (best == kNoKey || key > best) {  // ties: the newer level's stays
           best = key;
           level = l;
@@ -2761,18 +2913,18 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_predecessor(LevelSet lv, T
     uint32_t at = 0u;
     while (best != kNoKey) {
       at = run_start(lv, level, cur[level * kQueryThreads] - 1u, best);
-      if ((as_global(lv.kv[level])[at] & 1u) != 0u) break;
+      if ((as_global(lv.v[level].kv)[at] & 1u) != 0u) break;
       const uint32_t gone = best;
       best = kNoKey;
       for (int l = 0; l < lv.count; ++l) {
         uint32_t p = cur[l * kQueryThreads];
         if (p == 0u) continue;
-        uint32_t key = lv.kv[l][p - 1u] >> 1;
+        uint32_t key = lv.v[l].kv[p - 1u] >> 1;
         if (key == gone) {
           p = run_start(lv, l, p - 1u, gone);
           cur[l * kQueryThreads] = p;
           if (p == 0u) continue;
-          key = lv.kv[l][p - 1u] >> 1;
+          key = lv.v[l].kv[p - 1u] >> 1;
         }
         if (best == kNoKey || key > best) {
           best = key;
@@ -2783,7 +2935,7 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_predecessor(LevelSet lv, T
     if (i < nq) {
       const bool f = best != kNoKey;
       out_key[i] = f ? best : 0u;
-      out_val[i] = f ? as_global(lv.val[level])[at] : 0u;
+      out_val[i] = f ? as_global(lv.v[level].val)[at] : 0u;
       out_found[i] = f ? 1 : 0;
     }
   }
@@ -3150,39 +3302,55 @@ hipError_t launch_fill_runs(uint32_t* a_kv, uint32_t* a_val, uint32_t* b_kv, uin
                 b_val, n);
 }
 
-// Tops and grid of a query kernel that strides over the queries.  Up to
-// kFewQueries the work-groups run side by side and loading the tops is part of
-// every query's latency, so only what one round of loads brings (64 queries on
-// five levels: 23.7 us with 2048 words, 30.1 with 8192); above, the grid is as
-// large as keeps the loading of the tops small beside the queries (with one
-// level 2^22 lookups take 212 us in 4096 work-groups, 222 in 1280).
+// Levels with their tops, and the grid of a query kernel that strides over the
+// queries.  Up to kFewQueries the work-groups run side by side and loading the
+// tops would be part of every query's latency: 100 lookups on one, three and
+// five levels take 8.4, 15.7 and 24.6 us without them, 8.7, 18.2 and 26.2
+// with 8 KB of them.  Above, the grid is as large as keeps the loading of the
+// tops small beside the queries (with one level 2^22 lookups take 212 us in 4096
+// work-groups, 222 in 1280).
 constexpr uint32_t kFewQueries = 1u << 16;
-constexpr uint32_t kTopWordsFew = 2048;
-static TopSet query_tops(const LevelSet& lv, uint32_t nq) {
-  return top_set(lv, nq <= kFewQueries ? kTopWordsFew : kTopWords);
+static QLevels query_levels_for(const LevelSet& lv, uint32_t nq) {
+  return query_levels(lv, nq <= kFewQueries ? 0u : kTopWords);
 }
-static unsigned query_grid(const TopSet& ts, uint64_t nq) {
-  const uint64_t g = (nq + kQueryThreads - 1) / kQueryThreads;
-  const uint64_t most = 5u * 256u * (8192u / (ts.words > 2048u ? ts.words : 2048u));
+static unsigned query_grid(const QLevels& q, uint64_t nq, uint32_t per = 8) {
+  const uint64_t block = kQueryThreads / 8 * per, g = (nq + block - 1) / block;
+  const uint64_t most = 5u * 256u * (8192u / (q.words > 2048u ? q.words : 2048u));
   return static_cast<unsigned>(g < most ? g : most);
+}
+// Queries per octet of the several-level walks: eight, one after another, when
+// that leaves 2048 waves or more (8 on each of 256 CUs), else fewer, down to
+// one: 26 000 ranges of 32 keys on three levels take 91 us one at a time, 256
+// eight; 60 000 counts on ten levels 92 us by two, 144 by one.
+static uint32_t queries_per_octet(uint32_t nq) {
+  uint32_t per = 8;
+  while (per > 1 && nq / (8u * per) < 2048u) per /= 2;
+  return per;
+}
+// LDS words of the several-level walk of one work-group.
+static unsigned walk_lds_words(const QLevels& q, bool emit) {
+  return q.count <= 1 ? 0u : kQueryWaves * walk_words(static_cast<uint32_t>(q.count), emit);
 }
 
 hipError_t launch_lookup(const LevelSet& lv, const uint32_t* q, uint32_t nq, uint32_t* out_val,
                          uint8_t* out_found, hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  const TopSet ts = query_tops(lv, nq);
-  return launch_lds(k_lookup, query_grid(ts, nq), kQueryThreads, ts.words * 4u, stream, t, lv, ts,
-                    q, nq, out_val, out_found);
+  const QLevels ql = query_levels_for(lv, nq);
+  return launch_lds(ql.words != 0 ? k_lookup<true> : k_lookup<false>, query_grid(ql, nq), kQueryThreads, ql.words * 4u, stream, t, ql, q,
+                    nq, out_val, out_found);
 }
 
 hipError_t launch_count(const LevelSet& lv, const uint32_t* lo, const uint32_t* hi, uint32_t nq,
                         uint32_t* counts, uint64_t* scan_status, size_t scan_words,
                         uint32_t* bounds, hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  auto k = lv.count <= 1 ? k_count<1> : lv.count <= 8 ? k_count<8> : lv.count <= 16 ? k_count<16>
-                                                                           : k_count<kMaxLevels>;
-  const TopSet ts = query_tops(lv, nq);
-  return launch_lds(k, query_grid(ts, nq), kQueryThreads, ts.words * 4u, stream, t, lv, ts, lo, hi, nq,
+    const QLevels ql = query_levels_for(lv, nq);
+  const bool top = ql.words != 0;
+  auto k = lv.count <= 1 ? (top ? k_count<true, false> : k_count<false, false>)
+                         : (top ? k_count<true, true> : k_count<false, true>);
+  const unsigned lds = (ql.words + walk_lds_words(ql, false)) * 4u;
+  const uint32_t per = lv.count <= 1 ? 8u : queries_per_octet(nq);
+  return launch_lds(k, query_grid(ql, nq, per), kQueryThreads, lds, stream, t, ql, lo, hi, nq, per,
                     counts, scan_status, static_cast<uint64_t>(scan_words), bounds);
 }
 
@@ -3200,9 +3368,9 @@ hipError_t launch_successor(const LevelSet& lv, const uint32_t* q, uint32_t nq, 
                             uint32_t* out_val, uint8_t* out_found, hipStream_t stream,
                             const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  const TopSet ts = query_tops(lv, nq);
-  const unsigned lds = (ts.words + static_cast<unsigned>(lv.count) * kQueryThreads) * 4u;
-  return launch_lds(k_successor, query_grid(ts, nq), kQueryThreads, lds, stream, t, lv, ts, q, nq,
+  const QLevels ql = query_levels_for(lv, nq);
+  const unsigned lds = (ql.words + static_cast<unsigned>(ql.count) * kQueryThreads) * 4u;
+  return launch_lds(ql.words != 0 ? k_successor<true> : k_successor<false>, query_grid(ql, nq), kQueryThreads, lds, stream, t, ql, q, nq,
                     out_key, out_val, out_found);
 }
 
@@ -3210,9 +3378,9 @@ hipError_t launch_predecessor(const LevelSet& lv, const uint32_t* q, uint32_t nq
                               uint32_t* out_key, uint32_t* out_val, uint8_t* out_found,
                               hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  const TopSet ts = query_tops(lv, nq);
-  const unsigned lds = (ts.words + static_cast<unsigned>(lv.count) * kQueryThreads) * 4u;
-  return launch_lds(k_predecessor, query_grid(ts, nq), kQueryThreads, lds, stream, t, lv, ts, q, nq,
+  const QLevels ql = query_levels_for(lv, nq);
+  const unsigned lds = (ql.words + static_cast<unsigned>(ql.count) * kQueryThreads) * 4u;
+  return launch_lds(ql.words != 0 ? k_predecessor<true> : k_predecessor<false>, query_grid(ql, nq), kQueryThreads, lds, stream, t, ql, q, nq,
                     out_key, out_val, out_found);
 }
 
@@ -3247,20 +3415,22 @@ hipError_t launch_range_emit(const LevelSet& lv, const uint32_t* lo, const uint3
   // Emission from stored bounds and emission that searches (no scratch) are
   // separate instantiations, so that the first keeps a smaller register
   // footprint and no LDS for the tops.
-  TopSet ts{};
-  if (bounds == nullptr) ts = query_tops(lv, nq);
+  const QLevels ql = bounds != nullptr ? query_levels(lv, 0) : query_levels_for(lv, nq);
+  const bool top = ql.words != 0;
   const unsigned grid = grid_for(nq, kQueryThreads);
   if (lv.count <= 1)
-    return launch_lds(bounds != nullptr ? k_range_emit_one<4, false> : k_range_emit_one<4, true>,
-                      grid, kQueryThreads, ts.words * 4u, stream, t, lv, ts, lo, hi, nq, offsets,
+    return launch_lds(bounds != nullptr ? k_range_emit_one<false, 4, false>
+                      : top             ? k_range_emit_one<true, 4, true>
+                                        : k_range_emit_one<false, 4, true>,
+                      grid, kQueryThreads, ql.words * 4u, stream, t, ql, lo, hi, nq, offsets,
                       bounds, out_keys, out_vals, cap);
-  auto k = bounds != nullptr
-               ? (lv.count <= 8 ? k_range_emit<8, false> : lv.count <= 16 ? k_range_emit<16, false>
-                                                                          : k_range_emit<kMaxLevels, false>)
-               : (lv.count <= 8 ? k_range_emit<8, true> : lv.count <= 16 ? k_range_emit<16, true>
-                                                                         : k_range_emit<kMaxLevels, true>);
-  return launch_lds(k, grid, kQueryThreads, ts.words * 4u, stream, t, lv, ts, lo, hi, nq, offsets,
-                    bounds, out_keys, out_vals, cap);
+  auto k = bounds != nullptr ? k_range_emit<false, false>
+           : top             ? k_range_emit<true, true>
+                             : k_range_emit<false, true>;
+  const unsigned lds = (ql.words + walk_lds_words(ql, true)) * 4u;
+  const uint32_t per = queries_per_octet(nq);
+  return launch_lds(k, grid_for(nq, kQueryThreads / 8 * per), kQueryThreads, lds, stream, t, ql,
+                    lo, hi, nq, per, offsets, bounds, out_keys, out_vals, cap);
 }
 
 }  // namespace lsm
