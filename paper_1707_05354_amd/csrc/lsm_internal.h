@@ -121,6 +121,7 @@ struct SortMeta {
   uint32_t* bucket_n;     // this slot's [kTopBuckets] record: each top-digit bucket's size
                           // (its share per batch for a group) in the slot's last bucket
                           // sort (top-digit sort)
+  uint32_t* pad;          // this slot's padding element: key variable, value (4 words)
   uint32_t num_sort_tiles;
   int parity;
 };
@@ -178,6 +179,13 @@ struct SortArgs {
   const uint32_t* grp_cnt[kMaxGroup];
   uint32_t* grp_n[kMaxGroup];
   uint32_t grp_off[kMaxGroup];
+  // Padding is not scattered: batch q has grp_real[q] elements, and the
+  // b - grp_real[q] copies of its last one (at grp_pad[q]) are written by the
+  // bucket sort in front of it.
+  uint32_t grp_real[kMaxGroup];
+  const uint32_t* grp_pad[kMaxGroup];
+  uint32_t pads;            // copies over the whole group
+  int pad_shift;            // bit position of the top digit
   int path;                 // SortPath; both paths give the same order
   uint32_t* skew_out;       // optional: receives the largest top-digit bucket of an
                             // earlier sort (a hint for the choice of the next sorts)

@@ -1137,16 +1137,32 @@ struct ScatterLds {
   uint32_t rmax[kWaves];
 };
 
-__device__ void tile_scatter(const SortArgs& a, int top_shift, uint32_t tile, ScatterLds& S) {
+// What the tile half needs (a launch reads its arguments afresh, so they are
+// kept short).
+struct ScatterArgs {
+  BatchSrc src;
+  uint32_t* kv;         // the slot's scattered batch
+  uint32_t* val;
+  uint32_t* tile_cnt;   // its group starts
+  uint32_t* bucket_n;   // its bucket-size record
+  uint32_t* pad;        // its padding element
+  uint32_t* skew_out;
+  uint64_t* progress;
+  uint64_t seq;
+  int top_shift;
+};
+
+__device__ void tile_scatter(const ScatterArgs& a, uint32_t tile, ScatterLds& S) {
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const SortMeta& m = a.meta;
-  const uint32_t b = a.src.b;
+  BatchSrc src = a.src;
+  src.b = src.n;  // the padding is not scattered
+  const uint32_t b = src.b;
   const uint32_t tbase = tile * kSortTile;
   const uint32_t d0 = tid * kTopPer;
   static_assert(kTopPer == 4 && kSortTile < 65536, "four digits per thread, 16-bit starts");
   uint32_t kv[kSortItems], val[kSortItems], off[kSortItems], dg[kSortItems], key[kSortItems];
   bool valid[kSortItems];
-  tile_items<kSortItems>(a.src, tbase, wave, lane, kv, val, key, valid);
+  tile_items<kSortItems>(src, tbase, wave, lane, kv, val, key, valid);
   if (tile == 0 && tid == 0 && a.progress != nullptr)
     __hip_atomic_store(a.progress, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   // Tile 0 hands over the largest bucket of the slot's previous bucket sort
@@ -1155,12 +1171,12 @@ __device__ void tile_scatter(const SortArgs& a, int top_shift, uint32_t tile, Sc
   static_assert(kTopBuckets == 4 * kThreads, "four bucket records per thread");
   const bool hand = tile == 0 && a.skew_out != nullptr;
   uint4 rec4 = make_uint4(0u, 0u, 0u, 0u);
-  if (hand) rec4 = reinterpret_cast<const uint4*>(m.bucket_n)[tid];
+  if (hand) rec4 = reinterpret_cast<const uint4*>(a.bucket_n)[tid];
   // Rank the tile: each wave clears and fills its own tables.
   for (uint32_t i = lane; i < kTopBuckets / 2; i += 64) S.wcnt[wave][i] = 0u;
   for (uint32_t i = lane; i < 2 * (kHalf + 1); i += 64) (&S.u.mask[wave][0][0])[i] = 0ull;
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) dg[i] = (kv[i] >> top_shift) & (kTopBuckets - 1);
+  for (int i = 0; i < kSortItems; ++i) dg[i] = (kv[i] >> a.top_shift) & (kTopBuckets - 1);
   wave_rank_items(dg, valid, S.u.mask[wave][0], S.u.mask[wave][1], S.wcnt[wave], off);
   __syncthreads();  // every wave is done with its tables: S.u.local may be written
   // This thread's four digits are the halves of words d0 / 2 and d0 / 2 + 1;
@@ -1224,20 +1240,24 @@ __device__ void tile_scatter(const SortArgs& a, int top_shift, uint32_t tile, Sc
   }
   // Global writes last, so that no barrier waits for them: the group starts
   // and the grouped tile.
-  uint32_t* row = m.tile_cnt + static_cast<size_t>(tile) * (kTopBuckets / 2);
+  uint32_t* row = a.tile_cnt + static_cast<size_t>(tile) * (kTopBuckets / 2);
   row[2 * tid] = start[0] | (start[1] << 16);
   row[2 * tid + 1] = start[2] | (start[3] << 16);
+  if (tile == 0 && tid == 0 && a.src.n < a.src.b) {  // the batch's last element
+    a.pad[0] = kv[0];
+    a.pad[1] = val[0];
+  }
   const uint32_t tile_n = (b - tbase) < static_cast<uint32_t>(kSortTile) ? (b - tbase) : kSortTile;
   for (uint32_t x = tid; x < tile_n; x += kThreads) {
-    a.tmp_kv[0][tbase + x] = S.kv[x];
-    a.tmp_val[0][tbase + x] = S.val[x];
+    a.kv[tbase + x] = S.kv[x];
+    a.val[tbase + x] = S.val[x];
   }
   (void)key;
 }
 
-__global__ __launch_bounds__(kThreads) void k_msd_scatter(SortArgs a, int top_shift) {
+__global__ __launch_bounds__(kThreads) void k_msd_scatter(ScatterArgs a) {
   __shared__ ScatterLds S;
-  tile_scatter(a, top_shift, blockIdx.x, S);
+  tile_scatter(a, blockIdx.x, S);
 }
 
 struct alignas(16) LocalLds {
@@ -1250,6 +1270,10 @@ struct alignas(16) LocalLds {
   const uint32_t* run_k[kMaxFuse + 1];  // fused load: source of each run
   const uint32_t* run_v[kMaxFuse + 1];
   uint32_t run_delta[kMaxFuse + 1];
+  uint32_t pad_at[kMaxGroup];  // place of each batch's padding in the bucket's output
+  // Merge of runs larger than LDS: each run's next element, its end, the part
+  // of it in LDS and how much of that is merged.
+  uint32_t cur[kMaxFuse + 1], len[kMaxFuse + 1], win[kMaxFuse + 2], cut[kMaxFuse + 1];
 };
 
 // One stable counting pass over n <= kLocalCap elements in LDS, from
@@ -1296,15 +1320,17 @@ __device__ void lds_pass(LocalLds& L, int from, uint32_t n, int shift) {
 // gathered from the tile-major scatter (group table segb / segp over ntiles
 // tiles) into one of two global buffers at the bucket's own range: the
 // output (out_kv at s) or the second scratch buffer (tmp_kv[1] at s), chosen
-// so that the passes, ping-ponging between the two, end in the output.
-// Nothing else reads either range.
+// so that the passes, ping-ponging between the two, end in the output (or, to
+// leave room for padding, in the scratch buffer: to_tmp).  Nothing else reads
+// either range.
 __device__ void local_sort_streaming(const SortArgs& a, int lo_bit, int passes, uint32_t s,
                                      uint32_t n, LocalLds& L, const uint32_t* segb,
-                                     const uint32_t* segp, uint32_t ntiles) {
+                                     const uint32_t* segp, uint32_t ntiles, bool to_tmp) {
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t* bk[2] = {a.out_kv + s, a.tmp_kv[1] + s};
   uint32_t* bv[2] = {a.out_val + s, a.tmp_val[1] + s};
-  const int first = passes & 1;
+  const int first = (passes & 1) ^ (to_tmp ? 1 : 0);
+  uint32_t* fence = to_tmp ? nullptr : a.out_fence;
   for (uint32_t x = tid; x < n; x += kThreads) {
     uint32_t g = 0;
     for (uint32_t step = 1u << (31 - __builtin_clz(ntiles)); step > 0; step >>= 1) {
@@ -1315,7 +1341,7 @@ __device__ void local_sort_streaming(const SortArgs& a, int lo_bit, int passes, 
     const uint32_t k = a.tmp_kv[0][at];
     bk[first][x] = k;
     bv[first][x] = a.tmp_val[0][at];
-    if (passes == 0) put_fence(a.out_fence, a.out_n, s + x, k);
+    if (passes == 0) put_fence(fence, a.out_n, s + x, k);
   }
   if (passes == 0) return;
   __threadfence_block();
@@ -1324,7 +1350,7 @@ __device__ void local_sort_streaming(const SortArgs& a, int lo_bit, int passes, 
   uint32_t* chunk_cnt = L.k[1];
   for (int p = 0; p < passes; ++p) {
     const int shift = lo_bit + kRadixBits * p;
-    const int cur = first ^ (p & 1);  // the last pass writes buffer 0, the output
+    const int cur = first ^ (p & 1);  // the last pass writes buffer 0 (to_tmp: 1)
     const uint32_t* ik = bk[cur];
     const uint32_t* iv = bv[cur];
     uint32_t* ok = bk[cur ^ 1];
@@ -1372,7 +1398,7 @@ __device__ void local_sort_streaming(const SortArgs& a, int lo_bit, int passes, 
           if (o < n) {
             ok[o] = kv[i];
             ov[o] = vv[i];
-            if (p == passes - 1) put_fence(a.out_fence, a.out_n, s + o, kv[i]);
+            if (p == passes - 1) put_fence(fence, a.out_n, s + o, kv[i]);
           }
         }
       }
@@ -1383,12 +1409,12 @@ __device__ void local_sort_streaming(const SortArgs& a, int lo_bit, int passes, 
   }
 }
 
-// Stable merge in LDS of a = src[0, A) (newer) and b = src[A, A + c)
-// (older) into dst[0, A + c), a first on equal original keys.  Each thread
+// Stable merge in LDS of a = src[0, A) (newer) and b = src[B, B + c), B >= A
+// (older), into dst[0, A + c), a first on equal original keys.  Each thread
 // finds the merge-path split of its share of the output by binary search,
 // then merges it sequentially.  Ends with a barrier.
-__device__ void lds_merge_pair(const uint32_t* sk, const uint32_t* sv, uint32_t A, uint32_t c,
-                               uint32_t* dk, uint32_t* dv) {
+__device__ void lds_merge_pair(const uint32_t* sk, const uint32_t* sv, uint32_t A, uint32_t B,
+                               uint32_t c, uint32_t* dk, uint32_t* dv) {
   const uint32_t total = A + c;
   const uint32_t per = (total + kThreads - 1) / kThreads;
   const uint32_t d0 = threadIdx.x * per < total ? threadIdx.x * per : total;
@@ -1396,13 +1422,13 @@ __device__ void lds_merge_pair(const uint32_t* sk, const uint32_t* sv, uint32_t 
   uint32_t lo = d0 > c ? d0 - c : 0, hi = d0 < A ? d0 : A;
   while (lo < hi) {
     const uint32_t mid = (lo + hi) >> 1;
-    if ((sk[mid] >> 1) <= (sk[A + d0 - 1 - mid] >> 1)) lo = mid + 1;
+    if ((sk[mid] >> 1) <= (sk[B + d0 - 1 - mid] >> 1)) lo = mid + 1;
     else hi = mid;
   }
   uint32_t ia = lo, ib = d0 - lo;
   for (uint32_t o = d0; o < d1; ++o) {
-    const bool take_a = ia < A && (ib >= c || (sk[ia] >> 1) <= (sk[A + ib] >> 1));
-    const uint32_t src = take_a ? ia : A + ib;
+    const bool take_a = ia < A && (ib >= c || (sk[ia] >> 1) <= (sk[B + ib] >> 1));
+    const uint32_t src = take_a ? ia : B + ib;
     dk[o] = sk[src];
     dv[o] = sv[src];
     ia += take_a ? 1u : 0u;
@@ -1468,6 +1494,144 @@ __device__ __forceinline__ uint32_t seg_bound(const uint32_t* s, uint32_t lo, ui
   return lo;
 }
 
+// First position of the sorted run kv in [lo, hi) whose key is above k; the
+// whole wave searches, 64 positions a round.
+__device__ uint32_t wave_upper(const uint32_t* kv, uint32_t lo, uint32_t hi, uint32_t k) {
+  const uint32_t lane = lane_id();
+  while (lo < hi) {
+    const uint32_t len = hi - lo, step = (len + 63u) / 64u;
+    const uint64_t at = static_cast<uint64_t>(lo) + static_cast<uint64_t>(lane + 1) * step - 1;
+    const bool below = at < hi && (as_global(kv)[at] >> 1) <= k;
+    const uint32_t c = static_cast<uint32_t>(__popcll(ballot(below)));
+    const uint64_t nlo = static_cast<uint64_t>(lo) + static_cast<uint64_t>(c) * step;
+    const uint64_t nhi = nlo + step - 1;
+    lo = nlo < hi ? static_cast<uint32_t>(nlo) : hi;
+    hi = nhi < hi ? static_cast<uint32_t>(nhi) : hi;
+  }
+  return lo;
+}
+
+// Merges R sorted runs in global memory (L.run_k / L.run_v, L.len elements
+// each, newest first, L.cur = 0) and calls out(i, kv, value) for every output
+// position i in turn, newer elements first on equal original keys.  The runs
+// are taken part by part: a share of each (by its length) is read into LDS;
+// what lies below the smallest last key among the parts that do not end their
+// run is complete and is merged pairwise, as the cascade merges whole levels.
+// When nothing lies below it, a run of that key fills its part: then the key's
+// whole runs are copied, newest first.  Hot keys and padding, which make a
+// bucket large, so cost a copy: a bucket with 25 000 copies of one key takes
+// about 30 us, 330 when every element was ranked by searches in the others.
+template <typename Out>
+__device__ void merge_large(LocalLds& L, int R, Out out) {
+  const uint32_t tid = threadIdx.x, wave = tid >> 6;
+  constexpr int kPer = kLocalCap / kThreads;
+  uint32_t o = 0;
+  for (;;) {
+    uint32_t rest = 0;
+    for (int r = 0; r < R; ++r) rest += L.len[r] - L.cur[r];
+    if (rest == 0) break;
+    if (tid == 0) {
+      uint32_t at = 0;
+      for (int r = 0; r < R; ++r) {
+        const uint32_t m = L.len[r] - L.cur[r];
+        const uint32_t share = static_cast<uint32_t>(
+            static_cast<uint64_t>(kLocalCap - kMaxFuse - 1) * m / rest) + 1u;
+        L.win[r] = at;
+        at += rest <= static_cast<uint32_t>(kLocalCap) || m < share ? m : share;
+      }
+      L.win[R] = at;
+    }
+    __syncthreads();
+    const uint32_t W = L.win[R];
+    uint32_t rk[kPer], rv[kPer], run[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const uint32_t x = tid + i * kThreads;
+      run[i] = 0;
+      if (x < W) {
+        uint32_t r = 0;
+        while (static_cast<int>(r) + 1 < R && L.win[r + 1] <= x) ++r;
+        const uint32_t at = L.cur[r] + (x - L.win[r]);
+        run[i] = r;
+        rk[i] = as_global(L.run_k[r])[at];
+        rv[i] = as_global(L.run_v[r])[at];
+      }
+    }
+    // Run r's part goes where the pairwise merges find it: run 0 in buffer 0,
+    // run r in the buffer that the merge of run r - 1 has left its output in.
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const uint32_t x = tid + i * kThreads;
+      if (x < W) {
+        const int to = run[i] == 0 || (run[i] & 1u) != 0 ? 0 : 1;
+        L.k[to][x] = rk[i];
+        L.v[to][x] = rv[i];
+      }
+    }
+    __syncthreads();
+    uint32_t B = 0xFFFFFFFFu;
+    for (int r = 0; r < R; ++r) {
+      const uint32_t w0 = L.win[r], w1 = L.win[r + 1];
+      if (w1 > w0 && w1 - w0 < L.len[r] - L.cur[r]) {
+        const uint32_t last = L.k[r == 0 || (r & 1) ? 0 : 1][w1 - 1] >> 1;
+        B = last < B ? last : B;
+      }
+    }
+    if (tid < static_cast<uint32_t>(R)) {
+      const uint32_t w0 = L.win[tid], w1 = L.win[tid + 1];
+      L.cut[tid] = B == 0xFFFFFFFFu
+                       ? w1 - w0
+                       : seg_bound(L.k[tid == 0 || (tid & 1u) ? 0 : 1], w0, w1, B, false) - w0;
+    }
+    __syncthreads();
+    uint32_t total = 0;
+    for (int r = 0; r < R; ++r) total += L.cut[r];
+    if (total != 0) {
+      int acc = 0;
+      uint32_t A = L.cut[0];
+      for (int r = 1; r < R; ++r) {
+        const uint32_t c = L.cut[r];
+        lds_merge_pair(L.k[acc], L.v[acc], A, L.win[r], c, L.k[1 - acc], L.v[1 - acc]);
+        acc = 1 - acc;
+        A += c;
+      }
+      for (uint32_t x = tid; x < total; x += kThreads) out(o + x, L.k[acc][x], L.v[acc][x]);
+      if (tid < static_cast<uint32_t>(R)) L.cur[tid] += L.cut[tid];
+    } else {
+      // The runs of key B (a run that does not start with it has none here).
+      for (int r = static_cast<int>(wave); r < R; r += kWaves) {
+        const uint32_t e = wave_upper(L.run_k[r], L.cur[r], L.len[r], B);
+        if ((tid & 63u) == 0) L.cut[r] = e - L.cur[r];
+      }
+      __syncthreads();
+      for (int r = 0; r < R; ++r) {
+        const uint32_t c = L.cut[r], at = L.cur[r];
+        const uint32_t* k = L.run_k[r];
+        const uint32_t* v = L.run_v[r];
+        for (uint32_t x0 = 0; x0 < c; x0 += 8 * kThreads) {
+          uint32_t ck[8], cv[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t x = x0 + i * kThreads + tid, xc = at + (x < c ? x : c - 1);
+            ck[i] = as_global(k)[xc];
+            cv[i] = as_global(v)[xc];
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t x = x0 + i * kThreads + tid;
+            if (x < c) out(o + total + x, ck[i], cv[i]);
+          }
+        }
+        total += c;
+      }
+      __syncthreads();
+      if (tid < static_cast<uint32_t>(R)) L.cur[tid] += L.cut[tid];
+    }
+    o += total;
+    __syncthreads();
+  }
+}
+
 // One work-group per top-digit bucket d.  The bucket is digit d's group in
 // every tile of the tile-major scatter, gathered in tile order (the batch's
 // order), and is sorted on the digits below the top one: by ranking up to
@@ -1487,6 +1651,9 @@ __device__ __forceinline__ uint32_t seg_bound(const uint32_t* s, uint32_t lo, ui
 // (key, run, position) is a strict total order, so the order is again the
 // cascade's.  Without fusion, the sort of a level records its buckets'
 // starts as that level's top-digit index.
+// kPads: some batch of the group is padded (another instantiation, so that full
+// batches pay nothing for it).
+template <bool kPads>
 __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t d, LocalLds& L) {
   const uint32_t tid = threadIdx.x;
   const SortMeta& m = a.meta;
@@ -1503,15 +1670,22 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
   // A group (consecutive batches sorted together, the newer first on equal
   // keys) has the newest batch's tiles, then the next older batch's, and so
   // on: nta group-table entries, one per thread.
-  const uint32_t ntiles = m.num_sort_tiles;
   const uint32_t G = a.group;
-  const uint32_t nta = G * ntiles;
+  auto tiles_of = [&](uint32_t q) {
+    return q < G ? (kPads ? (a.grp_real[q] + kSortTile - 1) / kSortTile : m.num_sort_tiles) : 0u;
+  };
+  const uint32_t t1 = tiles_of(0), t2 = t1 + tiles_of(1), t3 = t2 + tiles_of(2);
+  const uint32_t nta = t3 + tiles_of(3);
   static_assert(kMsdMaxTiles <= kThreads, "one tile per thread");
   static_assert(kMaxGroup == 4, "the batch of a tile is chosen among four");
   const uint32_t bq = tid >= nta ? 0u
-                    : (tid >= ntiles ? 1u : 0u) + (tid >= 2 * ntiles ? 1u : 0u) +
-                          (tid >= 3 * ntiles ? 1u : 0u);  // the tile's batch in the group
-  const uint32_t tt = tid < nta ? tid - bq * ntiles : 0u;  // tile in its batch
+                    : (tid >= t1 ? 1u : 0u) + (tid >= t2 ? 1u : 0u) +
+                          (tid >= t3 ? 1u : 0u);  // the tile's batch in the group
+  const uint32_t tt = tid < nta ? tid - (bq == 0 ? 0u : bq == 1 ? t1 : bq == 2 ? t2 : t3)
+                                : 0u;  // tile in its batch
+  const uint32_t real_q = !kPads  ? a.src.b
+                        : bq == 0 ? a.grp_real[0] : bq == 1 ? a.grp_real[1]
+                        : bq == 2 ? a.grp_real[2] : a.grp_real[3];
   const uint32_t* cnt_q = bq == 0 ? a.grp_cnt[0] : bq == 1 ? a.grp_cnt[1]
                         : bq == 2 ? a.grp_cnt[2] : a.grp_cnt[3];
   const uint32_t off_q = bq == 0 ? a.grp_off[0] : bq == 1 ? a.grp_off[1]
@@ -1539,7 +1713,7 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
   // the tile (the last digit's ends at the tile's size).
   const uint32_t g_st = (d & 1) ? seg_w0 >> 16 : seg_w0 & 0xFFFFu;
   const uint32_t tile_n =
-      tid < nta ? min(a.src.b - tt * kSortTile, static_cast<uint32_t>(kSortTile)) : 0u;
+      tid < nta ? min(real_q - tt * kSortTile, static_cast<uint32_t>(kSortTile)) : 0u;
   const uint32_t g_en = d + 1 < kTopBuckets ? (((d + 1) & 1) ? seg_w1 >> 16 : seg_w1 & 0xFFFFu)
                                             : tile_n;
   const uint32_t g_c = (tid < nta && g_en > g_st) ? g_en - g_st : 0u;
@@ -1567,8 +1741,51 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
     L.run_delta[0] = 0;
   }
   __syncthreads();
-  const uint32_t s = L.tmp[2 * kWaves];
+  uint32_t s = L.tmp[2 * kWaves];
   const uint32_t n = L.tmp[2 * kWaves + 1];
+  // Padding: the copies of smaller digits come before this bucket, and `here`
+  // has a bit for every batch whose copies belong into it.
+  uint32_t here = 0u, pad_kv[kMaxGroup], pad_n[kMaxGroup];
+  if constexpr (kPads) {
+#pragma unroll
+    for (uint32_t q = 0; q < kMaxGroup; ++q) {
+      pad_n[q] = q < G ? a.src.b - a.grp_real[q] : 0u;
+      pad_kv[q] = pad_n[q] != 0 ? a.grp_pad[q][0] : 0u;
+      const uint32_t pd = (pad_kv[q] >> a.pad_shift) & (kTopBuckets - 1);
+      s += pad_n[q] != 0 && pd < d ? pad_n[q] : 0u;
+      here |= pad_n[q] != 0 && pd == d ? 1u << q : 0u;
+    }
+  }
+  // Place in the bucket's output (padding included) of its element x.
+  auto place = [&](uint32_t x) {
+    uint32_t p = x;
+    if (kPads && here != 0) {
+#pragma unroll
+      for (uint32_t q = 0; q < kMaxGroup; ++q)
+        p += ((here >> q) & 1u) != 0 && x >= L.pad_at[q] ? pad_n[q] : 0u;
+    }
+    return p;
+  };
+  // Writes the bucket's padding; o: the output position of its first element.
+  auto write_pads = [&](uint32_t* kv, uint32_t* val, uint32_t* fence, uint64_t len, uint64_t o) {
+    if (!kPads || here == 0) return;
+#pragma unroll
+    for (uint32_t q = 0; q < kMaxGroup; ++q) {
+      if (((here >> q) & 1u) == 0) continue;
+      uint64_t p = o + L.pad_at[q];
+#pragma unroll
+      for (uint32_t y = 0; y < kMaxGroup; ++y)
+        p += ((here >> y) & 1u) != 0 && L.pad_at[y] < L.pad_at[q] ? pad_n[y] : 0u;
+      const uint64_t e = p + pad_n[q] < len ? p + pad_n[q] : len;
+      const uint32_t v = a.grp_pad[q][1];
+      for (uint64_t x = p + tid; x < e; x += kThreads) {
+        kv[x] = pad_kv[q];
+        val[x] = v;
+        put_fence(fence, len, x, pad_kv[q]);
+      }
+    }
+  };
+  if (kPads && tid < kMaxGroup) L.pad_at[tid] = 0u;
   // The sort's largest bucket, for the choice of the next sorts' path and
   // fused depth (only sizes that can change those choices are recorded).
   // Bucket d's size (for a group, its share per batch) goes to the record of
@@ -1740,9 +1957,38 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
       load_phase(std::integral_constant<int, kLocalCap / kThreads>{});
   }
   __syncthreads();  // the loaded runs, fields and L.lo / L.rs
+  // A batch's padding stands before its last element, the first of its tile 0:
+  // how many elements of the bucket come before that one, then how many of
+  // the fused levels (those with a smaller key).
+  if (kPads && here != 0) {
+    if (n <= static_cast<uint32_t>(kLocalCap)) {
+#pragma unroll
+      for (uint32_t q = 0; q < kMaxGroup; ++q) {
+        if (((here >> q) & 1u) == 0) continue;
+        const uint32_t xq = segp[q == 0 ? 0u : q == 1 ? t1 : q == 2 ? t2 : t3];
+        const uint32_t fq = (pad_kv[q] >> lo_bit) & fmask;
+        uint32_t c = 0;
+        for (uint32_t x = tid; x < n; x += kThreads) {
+          const uint32_t f = (L.k[0][x] >> lo_bit) & fmask;
+          c += f < fq || (f == fq && x < xq) ? 1u : 0u;
+        }
+        if (c != 0) atomicAdd(&L.pad_at[q], c);
+      }
+    }
+    if (fused && tid < 32u && static_cast<int>(tid & 7u) < f.nlev && ((here >> (tid >> 3)) & 1u) != 0) {
+      const uint32_t q = tid >> 3, l = tid & 7u;
+      const uint32_t key = (q == 0 ? pad_kv[0] : q == 1 ? pad_kv[1] : q == 2 ? pad_kv[2] : pad_kv[3]) >> 1;
+      const uint32_t b0 = L.rs[l + 1], b1 = L.rs[l + 2];
+      const uint32_t c = levels_in_lds
+                             ? seg_bound(L.k[((l + 1) & 1u) ? buf : 1 - buf], b0, b1, key, false) - b0
+                             : seg_bound(f.kv[l] + L.lo[l], 0, b1 - b0, key, false);
+      if (c != 0) atomicAdd(&L.pad_at[q], c);
+    }
+    __syncthreads();
+  }
 
-  // ---- sort the batch's bucket.  sorted = true when it ends in LDS buffer
-  // buf, false when it was sorted in global memory (at out_k / out_v).
+  // ---- sort the batch's bucket.  sorted_lds: it ends in LDS buffer buf, else
+  // in global memory (at out_k / out_v).
   uint32_t* out_k = a.out_kv + s;
   uint32_t* out_v = a.out_val + s;
   bool sorted_lds = true;
@@ -1757,18 +2003,47 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
     }
   } else {
     sorted_lds = false;
-    local_sort_streaming(a, lo_bit, passes, s, n, L, segb, segp, nta);
+    if (kPads && here != 0) {
+#pragma unroll
+      for (uint32_t q = 0; q < kMaxGroup; ++q) {
+        if (((here >> q) & 1u) == 0) continue;
+        const uint32_t tq = q == 0 ? 0u : q == 1 ? t1 : q == 2 ? t2 : t3;
+        const uint32_t fq = (pad_kv[q] >> lo_bit) & fmask;
+        uint32_t c = 0;
+        for (uint32_t g = 0; g < nta; ++g) {
+          const uint32_t end = g + 1 < nta ? segp[g + 1] : n;
+          for (uint32_t x = segp[g] + tid; x < end; x += kThreads) {
+            const uint32_t y = (a.tmp_kv[0][segb[g] + (x - segp[g])] >> lo_bit) & fmask;
+            c += y < fq || (y == fq && x < segp[tq]) ? 1u : 0u;
+          }
+        }
+        if (c != 0) atomicAdd(&L.pad_at[q], c);
+      }
+    }
+    const bool to_tmp = kPads && here != 0 && !fused;
+    local_sort_streaming(a, lo_bit, passes, s, n, L, segb, segp, nta, to_tmp);
+    if (to_tmp) {
+      __threadfence_block();
+      __syncthreads();
+      for (uint32_t x = tid; x < n; x += kThreads) {
+        const uint32_t k = a.tmp_kv[1][s + x], p = place(x);
+        out_k[p] = k;
+        out_v[p] = a.tmp_val[1][s + x];
+        put_fence(a.out_fence, a.out_n, s + p, k);
+      }
+    }
   }
 
   if (!fused) {
     if (sorted_lds) {
       for (uint32_t x = tid; x < n; x += kThreads) {
-        const uint32_t k = L.k[buf][x];
-        out_k[x] = k;
-        out_v[x] = L.v[buf][x];
-        put_fence(a.out_fence, a.out_n, s + x, k);
+        const uint32_t k = L.k[buf][x], p = place(x);
+        out_k[p] = k;
+        out_v[p] = L.v[buf][x];
+        put_fence(a.out_fence, a.out_n, s + p, k);
       }
     }
+    write_pads(a.out_kv, a.out_val, a.out_fence, a.out_n, s);
     return;
   }
 
@@ -1780,11 +2055,11 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
     int acc = buf;
     for (int q = 1; q < R; ++q) {
       const uint32_t A = L.rs[q], c = L.rs[q + 1] - L.rs[q];
-      lds_merge_pair(L.k[acc], L.v[acc], A, c, L.k[1 - acc], L.v[1 - acc]);
+      lds_merge_pair(L.k[acc], L.v[acc], A, A, c, L.k[1 - acc], L.v[1 - acc]);
       acc = 1 - acc;
     }
     for (uint32_t x = tid; x < T; x += kThreads) {
-      const uint64_t pos = out0 + x;
+      const uint64_t pos = out0 + place(x);
       if (pos < f.out_len) {
         const uint32_t k = L.k[acc][x];
         f.out_kv[pos] = k;
@@ -1792,10 +2067,11 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
         put_fence(f.out_fence, f.out_len, pos, k);
       }
     }
+    write_pads(f.out_kv, f.out_val, f.out_fence, f.out_len, out0);
     return;
   }
 
-  // Runs too large for LDS: rank with searches in global memory.  The
+  // Runs too large for LDS: merged from global memory part by part.  The
   // batch's bucket is put in global scratch first (it may be in LDS).
   if (sorted_lds) {
     for (uint32_t x = tid; x < n; x += kThreads) {
@@ -1803,29 +2079,24 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
       out_v[x] = L.v[buf][x];
     }
   }
+  if (tid <= static_cast<uint32_t>(f.nlev)) {
+    const uint32_t q = tid;
+    L.run_k[q] = q == 0 ? out_k : f.kv[q - 1] + L.lo[q - 1];
+    L.run_v[q] = q == 0 ? out_v : f.val[q - 1] + L.lo[q - 1];
+    L.cur[q] = 0u;
+    L.len[q] = L.rs[q + 1] - L.rs[q];
+  }
   __threadfence_block();
   __syncthreads();
-  for (uint32_t e = tid; e < T; e += kThreads) {
-    int r = 0;
-    while (r + 1 < R && L.rs[r + 1] <= e) ++r;
-    const uint32_t p = e - L.rs[r];
-    const uint32_t* rkp = r == 0 ? out_k : f.kv[r - 1] + L.lo[r - 1];
-    const uint32_t* rvp = r == 0 ? out_v : f.val[r - 1] + L.lo[r - 1];
-    const uint32_t x = rkp[p];
-    const uint32_t key = x >> 1;
-    uint32_t rank = p;
-    for (int q = 0; q < R; ++q) {
-      if (q == r) continue;
-      const uint32_t* qk = q == 0 ? out_k : f.kv[q - 1] + L.lo[q - 1];
-      rank += seg_bound(qk, 0, L.rs[q + 1] - L.rs[q], key, q < r);
-    }
-    const uint64_t pos = out0 + rank;
+  merge_large(L, R, [&](uint32_t x, uint32_t k, uint32_t v) {
+    const uint64_t pos = out0 + place(x);
     if (pos < f.out_len) {
-      f.out_kv[pos] = x;
-      f.out_val[pos] = rvp[p];
-      put_fence(f.out_fence, f.out_len, pos, x);
+      f.out_kv[pos] = k;
+      f.out_val[pos] = v;
+      put_fence(f.out_fence, f.out_len, pos, k);
     }
-  }
+  });
+  write_pads(f.out_kv, f.out_val, f.out_fence, f.out_len, out0);
 }
 
 // Bucket work-group w (counted from the first bucket work-group) takes top
@@ -1836,9 +2107,10 @@ __device__ __forceinline__ uint32_t xcd_digit(uint32_t w) {
   return (w & 7u) * (kTopBuckets / 8) + (w >> 3);
 }
 
+template <bool kPads>
 __global__ __launch_bounds__(kThreads) void k_local_sort(SortArgs a, int lo_bit, int passes) {
   __shared__ LocalLds L;
-  bucket_sort(a, lo_bit, passes, xcd_digit(blockIdx.x), L);
+  bucket_sort<kPads>(a, lo_bit, passes, xcd_digit(blockIdx.x), L);
 }
 
 // One step of the pipelined top-digit sort: the first work-groups scatter
@@ -1853,12 +2125,13 @@ union StepLds {
 static_assert(sizeof(ScatterLds) <= sizeof(LocalLds),
               "the scatter half must not raise the step's LDS above the bucket sort's");
 
+template <bool kPads>
 __global__ __launch_bounds__(kThreads) void k_sort_step(SortArgs bk, int lo_bit, int passes,
-                                                        SortArgs sc, int top_shift) {
+                                                        ScatterArgs sc) {
   __shared__ StepLds U;
-  const uint32_t nt = sc.meta.num_sort_tiles;
-  if (blockIdx.x < nt) tile_scatter(sc, top_shift, blockIdx.x, U.S);
-  else bucket_sort(bk, lo_bit, passes, xcd_digit(blockIdx.x - nt), U.L);
+  const uint32_t nt = (sc.src.n + kSortTile - 1) / kSortTile;
+  if (blockIdx.x < nt) tile_scatter(sc, blockIdx.x, U.S);
+  else bucket_sort<kPads>(bk, lo_bit, passes, xcd_digit(blockIdx.x - nt), U.L);
 }
 
 // ------------------------------------------------------------ merge
@@ -3093,7 +3366,7 @@ hipError_t launch_zero_u64(uint64_t* p, hipStream_t stream) {
 size_t sort_meta_words(uint32_t b) {
   const size_t ns = grid_for(b, kSortTile);
   return static_cast<size_t>(2) * kMaxPasses * kRadix + static_cast<size_t>(kMaxPasses) * ns * kRadix +
-         kMaxPasses + 4 + kSortSlots * (ns * (kTopBuckets / 2) + kTopBuckets);
+         kMaxPasses + 4 + kSortSlots * (ns * (kTopBuckets / 2) + kTopBuckets + 4);
 }
 
 SortMeta sort_meta_carve(uint32_t* base, uint32_t b, int parity, int slot) {
@@ -3105,11 +3378,12 @@ SortMeta sort_meta_carve(uint32_t* base, uint32_t b, int parity, int slot) {
   m.tile_ctr = m.status + static_cast<size_t>(kMaxPasses) * ns * kRadix;
   m.err = m.tile_ctr + kMaxPasses;
   // Per slot: the group starts, then the bucket-size record (both 16-byte
-  // aligned).
+  // aligned), then the padding element.
   uint32_t* slot_base =
-      m.err + 4 + static_cast<size_t>(slot) * (ns * (kTopBuckets / 2) + kTopBuckets);
+      m.err + 4 + static_cast<size_t>(slot) * (ns * (kTopBuckets / 2) + kTopBuckets + 4);
   m.tile_cnt = slot_base;
   m.bucket_n = slot_base + ns * (kTopBuckets / 2);
+  m.pad = m.bucket_n + kTopBuckets;
   m.parity = parity;
   return m;
 }
@@ -3125,8 +3399,16 @@ static int bucket_passes(const SortArgs& a) {
   return (sort_top_shift(a) - a.lo_bit + kRadixBits - 1) / kRadixBits;
 }
 
+// Tiles of a batch's scatter: its elements', without the padding's.
+static uint32_t scatter_tiles(const SortArgs& a) { return grid_for(a.src.n, kSortTile); }
+
+static ScatterArgs scatter_args(const SortArgs& a) {
+  return ScatterArgs{a.src,      a.tmp_kv[0], a.tmp_val[0], a.meta.tile_cnt,  a.meta.bucket_n,
+                     a.meta.pad, a.skew_out,  a.progress,   a.seq, sort_top_shift(a)};
+}
+
 hipError_t launch_scatter(const SortArgs& a, hipStream_t stream, const KTimer* t) {
-  return launch(k_msd_scatter, a.meta.num_sort_tiles, kThreads, stream, t, a, sort_top_shift(a));
+  return launch(k_msd_scatter, scatter_tiles(a), kThreads, stream, t, scatter_args(a));
 }
 
 // The largest entry of a slot's bucket-size record into *out (one work-group).
@@ -3159,19 +3441,27 @@ SortArgs grouped(SortArgs a) {
     a.grp_cnt[0] = a.meta.tile_cnt;
     a.grp_n[0] = a.meta.bucket_n;
     a.grp_off[0] = 0;
+    a.grp_real[0] = a.src.n;
+    a.grp_pad[0] = a.meta.pad;
+    a.pads = a.src.b - a.src.n;
+    a.pad_shift = sort_top_shift(a);
   }
   return a;
 }
 
-hipError_t launch_buckets(const SortArgs& a, hipStream_t stream, const KTimer* t) {
-  return launch(k_local_sort, kTopBuckets, kThreads, stream, t, grouped(a), a.lo_bit,
-                bucket_passes(a));
+
+hipError_t launch_buckets(const SortArgs& in, hipStream_t stream, const KTimer* t) {
+  const SortArgs a = grouped(in);
+  return launch(a.pads != 0 ? k_local_sort<true> : k_local_sort<false>, kTopBuckets, kThreads,
+                stream, t, a, a.lo_bit, bucket_passes(a));
 }
 
-hipError_t launch_sort_step(const SortArgs& bk, const SortArgs& sc, hipStream_t stream,
+hipError_t launch_sort_step(const SortArgs& in, const SortArgs& sc, hipStream_t stream,
                             const KTimer* t) {
-  return launch(k_sort_step, sc.meta.num_sort_tiles + kTopBuckets, kThreads, stream, t,
-                grouped(bk), bk.lo_bit, bucket_passes(bk), sc, sort_top_shift(sc));
+  const SortArgs bk = grouped(in);
+  return launch(bk.pads != 0 ? k_sort_step<true> : k_sort_step<false>,
+                scatter_tiles(sc) + kTopBuckets, kThreads, stream, t, bk, bk.lo_bit,
+                bucket_passes(bk), scatter_args(sc));
 }
 
 hipError_t launch_sort(const SortArgs& a, hipStream_t stream, const KTimer* timers,

@@ -47,7 +47,9 @@ KERNEL_NAMES = ("k_sort_hist", "k_sort_pass", "k_merge", "k_lookup", "k_count", 
 # rocprofv3 kernel names behind each profiler kind that covers several kernels.
 KERNEL_TRACE_NAMES = {"k_order": ("k_successor", "k_predecessor"),
                       "k_clean": ("k_clean_count", "k_clean_scatter", "k_clean_pad"),
-                      "k_merge": ("k_merge<4>", "k_merge<8>", "k_merge<16>")}
+                      "k_merge": ("k_merge<4>", "k_merge<8>", "k_merge<16>"),
+                      "k_local_sort": ("k_local_sort<false>", "k_local_sort<true>"),
+                      "k_sort_step": ("k_sort_step<false>", "k_sort_step<true>")}
 _NK = len(KERNEL_NAMES)
 PROF_SIZES = 40  # LSM_PROF_SIZES
 
