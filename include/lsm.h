@@ -210,7 +210,7 @@ LSM_API lsm_status_t lsm_set_fusion(lsm_t h, int max_levels);
  * LSM_SORT_DIGIT_PASSES: one stable counting pass
  * per 8-bit digit with decoupled look-back.  LSM_SORT_AUTO (the default):
  * the top-digit sort unless the previous sort saw a top-digit bucket above
- * 1536 elements (skewed keys, where one work-group would sort a large bucket
+ * 16384 elements (skewed keys, where one work-group would sort a large bucket
  * alone).  Takes effect at the next sort.  LSM_EINVAL for another mode.
  */
 /*

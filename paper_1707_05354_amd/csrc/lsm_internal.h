@@ -126,14 +126,20 @@ struct SortMeta {
   int parity;
 };
 // The two sort paths: one scatter on the top digit then a per-bucket LDS
-// sort (for at most kMsdMaxTiles tiles), or one digit pass per 8 bits.  The
-// first is faster unless a top-digit bucket outgrows kLocalCap (skewed keys),
-// which its fallback handles with a single work-group; each sort records its
-// largest top-digit bucket so that the next sort can pick the path.
+// sort (for at most kMsdMaxTiles tiles), or one digit pass per 8 bits.  A
+// bucket that outgrows kLocalCap because of one key is still sorted by one
+// work-group at little more than a copy, so the first path is the faster one
+// as long as the largest bucket holds at most kMsdMaxBucket elements: Zipf(1.1)
+// keys whose first takes 8 % of a batch need 18 us a batch of 2^15 (2700 in its
+// bucket; 42 by digit passes), 45 of 2^17 (10 800; 56) and 157 of 2^19 (43 000;
+// 87).  Each sort records its largest top-digit bucket so that the next sort
+// can pick the path; one above kLocalCap that is not due to one key (or may not
+// be: a digit pass cannot tell) counts as above kMsdMaxBucket.
+constexpr uint32_t kMsdMaxBucket = 16384;
 enum SortPath : int { kSortMsd = 0, kSortLsd = 1 };
 inline int pick_sort_path(uint32_t tiles, uint32_t last_max_bucket) {
   return (tiles <= static_cast<uint32_t>(kMsdMaxTiles) &&
-          last_max_bucket <= static_cast<uint32_t>(kLocalCap))
+          last_max_bucket <= kMsdMaxBucket)
              ? kSortMsd
              : kSortLsd;
 }

@@ -138,6 +138,12 @@ __device__ void record_max(uint32_t x, uint32_t* out, uint32_t* tmp) {
   __syncthreads();
 }
 
+// What is recorded of a bucket of n elements that is not known to be large
+// because of one key: above the top-digit sort's limit when it outgrows LDS.
+__device__ __forceinline__ uint32_t large_bucket(uint32_t n) {
+  return n > static_cast<uint32_t>(kLocalCap) ? max(n, kMsdMaxBucket + 1) : n;
+}
+
 // Device-scope relaxed atomics for the look-back words: each word carries
 // its own payload, so no other memory needs ordering with it.
 __device__ __forceinline__ uint32_t ld_dev(const uint32_t* p) {
@@ -773,7 +779,8 @@ __global__ __launch_bounds__(kThreads) void k_sort_pass(SortArgs a, int pass) {
   const uint32_t tile = s_tile;
   if (tile != blockIdx.x) load_tile(tile);
   if (pass == 0 && tile == 0 && a.skew_out != nullptr)
-    record_max(mine[static_cast<size_t>(a.passes - 1) * kRadix + tid], a.skew_out, L.tmp);
+    record_max(large_bucket(mine[static_cast<size_t>(a.passes - 1) * kRadix + tid]), a.skew_out,
+               L.tmp);
   uint32_t* st = m.status + static_cast<size_t>(pass) * m.num_sort_tiles * kRadix;
   sort_tile_pass(kv, val, tile, b, a.lo_bit + kRadixBits * pass, st, o_kv, o_val,
                  (pass == a.passes - 1) ? a.out_fence : nullptr, false, &m.err[1], L);
@@ -1494,6 +1501,112 @@ __device__ __forceinline__ uint32_t seg_bound(const uint32_t* s, uint32_t lo, ui
   return lo;
 }
 
+// A bucket larger than LDS that is large because of one key: sorts it when the
+// most frequent key of 64 sampled elements holds all but kLocalCap of them.
+// Elements of equal keys are in order as they come, so that key's go straight
+// to their places and only the others are sorted, in LDS.  put(x, kv, value)
+// writes element x of the sorted bucket.  Each wave takes a quarter of the
+// groups, once to count and once to place.  Returns false, with nothing
+// written, when the bucket is not of this kind.
+template <typename Put>
+__device__ __forceinline__ bool sort_hot(const SortArgs& a, int lo_bit, int passes, uint32_t fmask, uint32_t n,
+                         LocalLds& L, uint32_t* fld, const uint32_t* segb, const uint32_t* segp,
+                         uint32_t nta, Put put) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto field = [&](uint32_t kv) { return (kv >> lo_bit) & fmask; };
+  // The sample, the same in every wave.
+  uint32_t g = 0;
+  const uint32_t sx = static_cast<uint32_t>((static_cast<uint64_t>(lane) * n) >> 6);
+  for (uint32_t step = 1u << (31 - __builtin_clz(nta)); step > 0; step >>= 1) {
+    const uint32_t probe = g + step;
+    if (probe < nta && segp[probe] <= sx) g = probe;
+  }
+  const uint32_t sf = field(a.tmp_kv[0][segb[g] + (sx - segp[g])]);
+  uint32_t same = 0;
+  for (int i = 0; i < 64; ++i)
+    same += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sf), i)) == sf ? 1u : 0u;
+  uint32_t best = (same << 6) | lane;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) best = max(best, static_cast<uint32_t>(__shfl_xor(best, o, 64)));
+  if ((best >> 6) < 4u) return false;
+  const uint32_t K = static_cast<uint32_t>(__shfl(static_cast<int>(sf), static_cast<int>(best & 63u), 64));
+  const uint32_t g0 = wave * nta / kWaves, g1 = (wave + 1) * nta / kWaves;
+  // each(kv, value, in): 256 elements of a group at a time, in order.
+  auto scan = [&](bool vals, auto each) {
+    for (uint32_t q = g0; q < g1; ++q) {
+      const uint32_t first = segb[q], c = (q + 1 < nta ? segp[q + 1] : n) - segp[q];
+      for (uint32_t j = 0; j < c; j += 256) {
+        uint32_t k[4], v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t x = j + 64 * u + lane;
+          const uint32_t at = first + (x < c ? x : c - 1);
+          k[u] = a.tmp_kv[0][at];
+          v[u] = vals ? a.tmp_val[0][at] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (j + 64 * u < c) each(k[u], v[u], j + 64 * u + lane < c);
+        }
+      }
+    }
+  };
+  uint32_t lt = 0, eq = 0, ne = 0;
+  scan(false, [&](uint32_t k, uint32_t, bool in) {
+    const uint32_t f = field(k);
+    lt += static_cast<uint32_t>(__popcll(ballot(in && f < K)));
+    eq += static_cast<uint32_t>(__popcll(ballot(in && f == K)));
+    ne += static_cast<uint32_t>(__popcll(ballot(in && f != K)));
+  });
+  if (lane == 0) {
+    L.win[wave] = lt;
+    L.len[wave] = eq;
+    L.cur[wave] = ne;
+  }
+  __syncthreads();
+  uint32_t n_lt = 0, n_eq = 0, m = 0, at_eq = 0, at_ne = 0;
+  for (uint32_t w = 0; w < kWaves; ++w) {
+    if (w == wave) {
+      at_eq = n_eq;
+      at_ne = m;
+    }
+    n_lt += L.win[w];
+    n_eq += L.len[w];
+    m += L.cur[w];
+  }
+  if (m > static_cast<uint32_t>(kLocalCap)) return false;
+  at_eq += n_lt;
+  const bool rank = m <= kRankSortMax;
+  scan(true, [&](uint32_t k, uint32_t v, bool in) {
+    const uint32_t f = field(k);
+    const uint64_t me = ballot(in && f == K), mn = ballot(in && f != K);
+    if (in && f == K) put(at_eq + count_below(me), k, v);
+    if (in && f != K) {
+      const uint32_t x = at_ne + count_below(mn);
+      L.k[0][x] = k;
+      L.v[0][x] = v;
+      if (rank) fld[x] = (f << 8) | x;
+    }
+    at_eq += static_cast<uint32_t>(__popcll(me));
+    at_ne += static_cast<uint32_t>(__popcll(mn));
+  });
+  if (rank && tid >= m && tid < ((m + 7u) & ~7u)) fld[tid] = 0xFFFFFFFFu;
+  __syncthreads();
+  int cur = 0;
+  if (rank) {
+    rank_sort(L, fld, m);
+    cur = 1;
+  } else {
+    for (int p = 0; p < passes; ++p) {
+      lds_pass(L, cur, m, lo_bit + kRadixBits * p);
+      cur = 1 - cur;
+    }
+  }
+  for (uint32_t x = tid; x < m; x += kThreads)
+    put(x < n_lt ? x : x + n_eq, L.k[cur][x], L.v[cur][x]);
+  return true;
+}
+
 // First position of the sorted run kv in [lo, hi) whose key is above k; the
 // whole wave searches, 64 positions a round.
 __device__ uint32_t wave_upper(const uint32_t* kv, uint32_t lo, uint32_t hi, uint32_t k) {
@@ -1522,7 +1635,7 @@ __device__ uint32_t wave_upper(const uint32_t* kv, uint32_t lo, uint32_t hi, uin
 // bucket large, so cost a copy: a bucket with 25 000 copies of one key takes
 // about 30 us, 330 when every element was ranked by searches in the others.
 template <typename Out>
-__device__ void merge_large(LocalLds& L, int R, Out out) {
+__device__ __forceinline__ void merge_large(LocalLds& L, int R, Out out) {
   const uint32_t tid = threadIdx.x, wave = tid >> 6;
   constexpr int kPer = kLocalCap / kThreads;
   uint32_t o = 0;
@@ -1792,11 +1905,9 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
   // every batch's slot with a plain store: every bucket sort writes all of
   // a record, so no atomics and no clearing are needed; the next scatter
   // into any of the slots takes the largest entry.
-  if (tid < G) {
-    uint32_t* rec = tid == 0 ? a.grp_n[0] : tid == 1 ? a.grp_n[1]
-                  : tid == 2 ? a.grp_n[2] : a.grp_n[3];
-    rec[d] = (n + G - 1) / G;
-  }
+  uint32_t* rec = tid == 0 ? a.grp_n[0] : tid == 1 ? a.grp_n[1]
+                : tid == 2 ? a.grp_n[2] : a.grp_n[3];
+  if (tid < G) rec[d] = (n + G - 1) / G;
   if (!fused && a.out_digit != nullptr && tid == 0) a.out_digit[d] = s;
   if (n == 0 && !fused) return;
 
@@ -2020,16 +2131,28 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
         if (c != 0) atomicAdd(&L.pad_at[q], c);
       }
     }
-    const bool to_tmp = kPads && here != 0 && !fused;
-    local_sort_streaming(a, lo_bit, passes, s, n, L, segb, segp, nta, to_tmp);
-    if (to_tmp) {
-      __threadfence_block();
+    if (kPads) __syncthreads();  // the paddings' places
+    const bool hot = sort_hot(a, lo_bit, passes, fmask, n, L, fld, segb, segp, nta,
+                              [&](uint32_t x, uint32_t k, uint32_t v) {
+                                const uint32_t p = fused ? x : place(x);
+                                out_k[p] = k;
+                                out_v[p] = v;
+                                if (!fused) put_fence(a.out_fence, a.out_n, s + p, k);
+                              });
+    if (!hot) {
+      if (tid < G) rec[d] = large_bucket((n + G - 1) / G);
+      const bool to_tmp = kPads && here != 0 && !fused;
       __syncthreads();
-      for (uint32_t x = tid; x < n; x += kThreads) {
-        const uint32_t k = a.tmp_kv[1][s + x], p = place(x);
-        out_k[p] = k;
-        out_v[p] = a.tmp_val[1][s + x];
-        put_fence(a.out_fence, a.out_n, s + p, k);
+      local_sort_streaming(a, lo_bit, passes, s, n, L, segb, segp, nta, to_tmp);
+      if (to_tmp) {
+        __threadfence_block();
+        __syncthreads();
+        for (uint32_t x = tid; x < n; x += kThreads) {
+          const uint32_t k = a.tmp_kv[1][s + x], p = place(x);
+          out_k[p] = k;
+          out_v[p] = a.tmp_val[1][s + x];
+          put_fence(a.out_fence, a.out_n, s + p, k);
+        }
       }
     }
   }

@@ -90,3 +90,27 @@ def test_hot_keys_in_a_large_bucket(hot):
         t.delete(k) if i % 6 == 4 else t.insert(k, values(rng, b))
     t.check_levels()
     t.g.close()
+
+
+@pytest.mark.parametrize("kind,paths", [("hot", "TTTTTT"), ("cluster", "TDDDDD"), ("spread", "TTTTTT")])
+def test_path_of_large_buckets(kind, paths):
+    """A bucket that outgrows LDS because of one key stays with the top-digit
+    sort (T); one of many keys goes to digit passes (D)."""
+    b = 1 << 15
+    note("path of large buckets: %s" % kind)
+    rng = np.random.default_rng(7)
+    t = Trio(b)
+    got = ""
+    for i in range(6):
+        k = rng.integers(0, 1 << 31, b, dtype=np.uint64).astype(np.uint32)
+        if kind == "hot":
+            k[rng.random(b) < 0.2] = 123456
+        elif kind == "cluster":
+            near = rng.random(b) < 0.2
+            k[near] = rng.integers(0, 1 << 20, near.sum())
+        before = t.g.stats().sorts_digit_passes
+        t.insert(k, values(rng, b))
+        t.check_levels()  # synchronises, so the next choice sees this sort
+        got += "D" if t.g.stats().sorts_digit_passes > before else "T"
+    assert got == paths
+    t.g.close()
