@@ -1,6 +1,6 @@
 // gfx950 kernels of the batched LSM dictionary.
 //
-// Every kernel runs in work-groups of four wave64 waves.  Nothing here is a
+// Most kernels run in work-groups of four wave64 waves.  Nothing here is a
 // dense contraction, so there is no MFMA: the batch sort and the level
 // merges are HBM/L2 streams, the searches are random-access.
 //
@@ -20,7 +20,8 @@
 //       the newer element first on equal keys (sec. IV-A), merge-path
 //       partitioned with a 64-ary wave search.
 //   k_lookup : per-query lower bound over the occupied levels, newest first,
-//       stopping at the first hit (sec. III-D, IV-B).
+//       stopping at the first hit (sec. III-D, IV-B).  k_lookup_few and
+//       k_count_few : the same for few queries, the levels dealt to the waves.
 //   k_count / k_range_emit : per-query bounds in every occupied level and a
 //       merge of the per-level candidate runs in level order, keeping the
 //       first element of each key run when it is a regular element
@@ -2521,13 +2522,12 @@ __global__ __launch_bounds__(kThreads) void k_fill_runs(uint32_t* a_kv, uint32_t
 // (1.39 ms with whole descents: then the addresser and the longer chain of
 // dependent loads bound it too); with one level 212 us (244).  Five waves a
 // SIMD hide the chain; at four (98 registers) ten levels take 1.10 ms.
-template <bool kTop>
 __global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(QLevels lv,
                                                              const uint32_t* q, uint32_t nq,
                                                              uint32_t* out_val,
                                                              uint8_t* out_found) {
   extern __shared__ uint32_t top[];
-  if constexpr (kTop) load_tops<kQueryThreads / 64>(lv, top);
+  load_tops<kQueryThreads / 64>(lv, top);
   for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
        q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
     // Every lane stays until the wave is done: the searches are wave-wide.
@@ -2542,7 +2542,7 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(QLevels lv,
     for (int l = 0; l < lv.count; ++l) {
       if (ballot(!done) == 0) break;
       bool hit;
-      const uint32_t p = octet_bound<kTop, false, true>(lv, top, l, k, kq, &hit);
+      const uint32_t p = octet_bound<true, false, true>(lv, top, l, k, kq, &hit);
       if (!done && hit && p < lv.v[l].len) {
         const uint32_t x = lv.v[l].kv[p], y = lv.v[l].val[p];
         if ((x >> 1) == k) {
@@ -2558,6 +2558,63 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_lookup(QLevels lv,
       out_val[i] = v;
       out_found[i] = f;
     }
+  }
+}
+
+// Few lookups: a work-group takes 64 queries and deals the levels to its waves
+// (up to kFewWaves, each with every kFewWaves-th level), so that the descents,
+// each a chain of dependent loads from memory, run side by side instead of one
+// after another; the newest level's answer is chosen at the end.  64 lookups on
+// five levels take 8 us, 22.5 level after level; 2^17 on ten take 60 us, 69.
+constexpr uint32_t kFewWaves = 8;
+static uint32_t few_waves(int levels) {
+  const uint32_t n = levels > 0 ? static_cast<uint32_t>(levels) : 1u;
+  return n < kFewWaves ? n : kFewWaves;
+}
+
+__global__ __launch_bounds__(64 * kFewWaves) void k_lookup_few(QLevels lv, const uint32_t* q,
+                                                               uint32_t nq, uint32_t* out_val,
+                                                               uint8_t* out_found) {
+  // Per wave and query: 4 l + 2 + status of the element found, and its value.
+  __shared__ uint32_t s_at[kFewWaves][64], s_val[kFewWaves][64];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const uint32_t waves = blockDim.x >> 6;
+  const uint32_t i = blockIdx.x * 64 + lane;
+  const bool active = i < nq;
+  const uint32_t k = active ? q[i] : 0u;
+  uint32_t kq[8];
+  octet_lanes(k, kq);
+  uint32_t at = ~0u, v = 0u;
+  for (int l = static_cast<int>(wave); l < lv.count; l += static_cast<int>(waves)) {
+    if (ballot(at == ~0u) == 0) break;
+    bool hit;
+    const uint32_t p = octet_bound<false, false, true>(lv, nullptr, l, k, kq, &hit);
+    if (at == ~0u && hit && p < lv.v[l].len) {
+      const uint32_t x = lv.v[l].kv[p], y = lv.v[l].val[p];
+      if ((x >> 1) == k) {
+        at = 4u * static_cast<uint32_t>(l) + 2u + (x & 1u);
+        v = y;
+      }
+    }
+  }
+  if (waves > 1) {
+    s_at[wave][lane] = at;
+    s_val[wave][lane] = v;
+    __syncthreads();
+    if (wave != 0) return;
+    for (uint32_t w = 1; w < waves; ++w) {
+      const uint32_t a = s_at[w][lane];
+      if (a < at) {  // a newer level's (the levels differ)
+        at = a;
+        v = s_val[w][lane];
+      }
+    }
+  }
+  if (active) {
+    const bool f = at != ~0u && (at & 1u) != 0u;
+    out_val[i] = f ? v : 0u;
+    out_found[i] = f ? 1 : 0;
   }
 }
 
@@ -2819,11 +2876,74 @@ __device__ __forceinline__ void walk_run(const QLevels& lv, const WalkLds& w, ui
   }
 }
 
+// This lane's share of the live keys of query qi (the same in all lanes of an
+// octet; every lane of the wave calls it).
+__device__ __forceinline__ uint32_t count_walk(const QLevels& lv, const WalkLds& w, uint32_t qi,
+                                               uint32_t h, bool live) {
+  const uint32_t sub = lane_id() & 7u;
+  uint32_t c = 0;
+  while (ballot(live) != 0) {
+    uint32_t B;
+    const uint32_t n = walk_chunk<false>(lv, w, qi, h, live, &B);
+    for (uint32_t i = sub; i < n; i += 8) c += list_valid(w.list, i, w.list[i]) ? 1u : 0u;
+    if (live && B != kNoKey && n == 0) {
+      uint32_t x = 0u, v = 0u;
+      walk_run<false>(lv, w, qi, B, &x, &v);
+      if (sub == 0) c += x & 1u;
+    }
+    live = live && B != kNoKey;
+  }
+  return c;
+}
+
 // An octet takes `per` queries (1, 2, 4 or 8): the query of a lane, counted from
 // the work-group's first.  With fewer than eight, lanes per .. 7 search along
 // with their octet's queries again and keep nothing.
 __device__ __forceinline__ uint32_t query_slot(uint32_t per) {
   return (threadIdx.x >> 3) * per + (threadIdx.x & (per - 1u));
+}
+
+// Count pass for few queries on several levels: 64 queries a work-group, the
+// levels' descents dealt to its eight waves as for few lookups, then an octet a
+// query: 3000 counts on five levels take 15 us, 28 with every wave
+// descending all levels; 2^17 on ten take 80 us, 118.  Stores what k_count stores.
+__global__ __launch_bounds__(64 * kFewWaves) void k_count_few(QLevels lv, const uint32_t* lo,
+                                                              const uint32_t* hi, uint32_t nq,
+                                                              uint32_t* counts,
+                                                              uint64_t* scan_status,
+                                                              uint64_t scan_words,
+                                                              uint32_t* bounds) {
+  extern __shared__ uint32_t top[];
+  if (scan_status != nullptr)
+    for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; w < scan_words;
+         w += static_cast<uint64_t>(gridDim.x) * blockDim.x)
+      scan_status[w] = 0ull;
+  const uint32_t lane = threadIdx.x & 63, sub = lane & 7u;
+  const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const uint32_t waves = blockDim.x >> 6, L = static_cast<uint32_t>(lv.count);
+  // One set of cursors for the work-group, a list for each octet.
+  WalkLds w;
+  w.cur = top;
+  w.list = top + 64u * L + (threadIdx.x >> 3) * walk_list(L);
+  w.vals = nullptr;
+  const uint32_t gi = blockIdx.x * 64 + lane;
+  const uint32_t k1 = gi < nq ? lo[gi] : 1u;
+  uint32_t kq[8];
+  octet_lanes(k1, kq);
+  for (uint32_t l = wave; l < L; l += waves) {
+    const uint32_t p =
+        octet_bound<false, false, false>(lv, nullptr, static_cast<int>(l), k1, kq, nullptr);
+    w.cur[l * 64 + lane] = p;
+    if (bounds != nullptr && gi < nq) bounds[static_cast<size_t>(l) * nq + gi] = p;
+  }
+  __syncthreads();
+  for (uint32_t qi = threadIdx.x >> 3; qi < 64u; qi += waves * 8u) {
+    const uint32_t qg = blockIdx.x * 64 + qi;
+    const uint32_t k2 = qg < nq ? hi[qg] : 0u;
+    const uint32_t h = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
+    const uint32_t c = octet_sum(count_walk(lv, w, qi, h, qg < nq));
+    if (sub == 0 && qg < nq) counts[qg] = c;
+  }
 }
 
 // Count pass.  With bounds non-null, each query's position in the levels is
@@ -2882,20 +3002,7 @@ __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
         const uint32_t qi = (lane & 56u) + r;
         const uint32_t h =
             static_cast<uint32_t>(__shfl(static_cast<int>(h2), static_cast<int>(qi), 64));
-        uint32_t c = 0;  // this lane's share of the count
-        bool live = true;
-        while (ballot(live) != 0) {
-          uint32_t B;
-          const uint32_t n = walk_chunk<false>(lv, w, qi, h, live, &B);
-          for (uint32_t i = sub; i < n; i += 8) c += list_valid(w.list, i, w.list[i]) ? 1u : 0u;
-          if (live && B != kNoKey && n == 0) {
-            uint32_t x = 0u, v = 0u;
-            walk_run<false>(lv, w, qi, B, &x, &v);
-            if (sub == 0) c += x & 1u;
-          }
-          live = live && B != kNoKey;
-        }
-        c = octet_sum(c);
+        const uint32_t c = octet_sum(count_walk(lv, w, qi, h, true));
         res = sub == r ? c : res;
       }
       if (active) counts[gi] = res;
@@ -3209,34 +3316,48 @@ __global__ __launch_bounds__(kThreads) void k_scan(const uint32_t* counts, uint3
 // stand in LDS (word l * kQueryThreads + thread), since an array indexed by
 // the level takes 148 registers: three waves a SIMD, 439 us for 2^20 queries
 // on seven levels; descending again from the dropped key takes 547.
-template <bool kTop>
-__global__ __launch_bounds__(kQueryThreads, 5) void k_successor(QLevels lv,
-                                                                const uint32_t* q, uint32_t nq,
-                                                                uint32_t* out_key,
-                                                                uint32_t* out_val,
-                                                                uint8_t* out_found) {
+// Few queries: 64 a work-group, the levels' descents dealt to its waves as for
+// few lookups; the first wave goes on from the cursors and elements they leave:
+// 500 queries on seven levels take 21 us (successor), 45 with every wave
+// descending all levels; 60 000 take 45 us, 60.
+template <bool kFew>
+__global__ __launch_bounds__(kFew ? 64 * kFewWaves : kQueryThreads, 5) void k_successor(
+    QLevels lv, const uint32_t* q, uint32_t nq, uint32_t* out_key, uint32_t* out_val,
+    uint8_t* out_found) {
+  constexpr uint32_t kStride = kFew ? 64 : kQueryThreads;
   extern __shared__ uint32_t top[];
-  uint32_t* cur = top + lv.words + threadIdx.x;
-  if constexpr (kTop) load_tops<kQueryThreads / 64>(lv, top);
-  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
-       q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
-    const uint64_t i = q0 + threadIdx.x;
+  const uint32_t slot = kFew ? threadIdx.x & 63u : threadIdx.x;
+  const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const int waves = static_cast<int>(blockDim.x >> 6);
+  uint32_t* cur = top + lv.words + slot;
+  uint32_t* elem = cur + static_cast<uint32_t>(lv.count) * kStride;  // few queries only
+  if constexpr (!kFew) load_tops<kQueryThreads / 64>(lv, top);
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kStride; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * kStride) {
+    const uint64_t i = q0 + slot;
     const uint32_t k = i < nq ? q[i] : kMaxKey;
     uint32_t kq[8];
     octet_lanes(k, kq);
     uint32_t best = kNoKey, x = 0u;  // the smallest key and its newest instance
     int level = 0;
-    for (int l = 0; l < lv.count; ++l) {
-      const uint32_t p = octet_bound<kTop, true, false>(lv, top, l, k, kq, nullptr);
-      cur[l * kQueryThreads] = p;
-      if (p < lv.v[l].len) {
-        const uint32_t y = lv.v[l].kv[p];
-        if ((y >> 1) < best) {  // ties: the newer level's stays
-          best = y >> 1;
-          x = y;
-          level = l;
-        }
+    auto take = [&](int l, uint32_t p, uint32_t y) {
+      if (p < lv.v[l].len && (y >> 1) < best) {  // ties: the newer level's stays
+        best = y >> 1;
+        x = y;
+        level = l;
       }
+    };
+    for (int l = kFew ? wave : 0; l < lv.count; l += kFew ? waves : 1) {
+      const uint32_t p = octet_bound<!kFew, true, false>(lv, top, l, k, kq, nullptr);
+      cur[l * kStride] = p;
+      const uint32_t y = p < lv.v[l].len ? lv.v[l].kv[p] : 0u;
+      if (kFew) elem[l * kStride] = y;
+      else take(l, p, y);
+    }
+    if constexpr (kFew) {
+      __syncthreads();
+      if (wave != 0) return;  // one block of queries a work-group
+      for (int l = 0; l < lv.count; ++l) take(l, cur[l * kStride], elem[l * kStride]);
     }
     if (k >= kMaxKey) best = kNoKey;
     while (best != kNoKey && (x & 1u) == 0u) {
@@ -3244,26 +3365,22 @@ __global__ __launch_bounds__(kQueryThreads, 5) void k_successor(QLevels lv,
       best = kNoKey;
       for (int l = 0; l < lv.count; ++l) {
         const uint32_t* kv = lv.v[l].kv;
-        uint32_t p = cur[l * kQueryThreads];
+        uint32_t p = cur[l * kStride];
         if (p >= lv.v[l].len) continue;
         uint32_t y = kv[p];
         if ((y >> 1) == gone) {
           p = skip_run(kv, p, lv.v[l].len, gone);
-          cur[l * kQueryThreads] = p;
+          cur[l * kStride] = p;
           if (p >= lv.v[l].len) continue;
           y = kv[p];
         }
-        if ((y >> 1) < best) {
-          best = y >> 1;
-          x = y;
-          level = l;
-        }
+        take(l, p, y);
       }
     }
     if (i < nq) {
       const bool f = best != kNoKey;
       out_key[i] = f ? best : 0u;
-      out_val[i] = f ? as_global(lv.v[level].val)[cur[level * kQueryThreads]] : 0u;
+      out_val[i] = f ? as_global(lv.v[level].val)[cur[level * kStride]] : 0u;
       out_found[i] = f ? 1 : 0;
     }
   }
@@ -3278,54 +3395,61 @@ __device__ __forceinline__ uint32_t run_start(const QLevels& lv, int l, uint32_t
 // Predecessor: the mirror walk, the largest key below the levels' lower bounds
 // of q; the newest instance is the first element of its run in the first level
 // that holds it.
-template <bool kTop>
-__global__ __launch_bounds__(kQueryThreads, 5) void k_predecessor(QLevels lv,
-                                                                  const uint32_t* q, uint32_t nq,
-                                                                  uint32_t* out_key,
-                                                                  uint32_t* out_val,
-                                                                  uint8_t* out_found) {
+template <bool kFew>
+__global__ __launch_bounds__(kFew ? 64 * kFewWaves : kQueryThreads, 5) void k_predecessor(
+    QLevels lv, const uint32_t* q, uint32_t nq, uint32_t* out_key, uint32_t* out_val,
+    uint8_t* out_found) {
+  constexpr uint32_t kStride = kFew ? 64 : kQueryThreads;
   extern __shared__ uint32_t top[];
-  uint32_t* cur = top + lv.words + threadIdx.x;  // the candidate is the element below
-  if constexpr (kTop) load_tops<kQueryThreads / 64>(lv, top);
-  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
-       q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
-    const uint64_t i = q0 + threadIdx.x;
+  const uint32_t slot = kFew ? threadIdx.x & 63u : threadIdx.x;
+  const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const int waves = static_cast<int>(blockDim.x >> 6);
+  uint32_t* cur = top + lv.words + slot;  // the candidate is the element below
+  uint32_t* elem = cur + static_cast<uint32_t>(lv.count) * kStride;  // few queries only
+  if constexpr (!kFew) load_tops<kQueryThreads / 64>(lv, top);
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kStride; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * kStride) {
+    const uint64_t i = q0 + slot;
     const uint32_t k = i < nq ? q[i] : 0u;
     uint32_t kq[8];
     octet_lanes(k, kq);
     uint32_t best = kNoKey;  // the largest key, kNoKey for none
     int level = 0;
-    for (int l = 0; l < lv.count; ++l) {
-      const uint32_t p = octet_bound<kTop, false, false>(lv, top, l, k, kq, nullptr);
-      cur[l * kQueryThreads] = p;
-      if (p > 0u) {
-        const uint32_t key = lv.v[l].kv[p - 1u] >> 1;
-        if (best == kNoKey || key > best) {  // ties: the newer level's stays
-          best = key;
-          level = l;
-        }
+    auto take = [&](int l, uint32_t p, uint32_t key) {
+      if (p > 0u && (best == kNoKey || key > best)) {  // ties: the newer level's stays
+        best = key;
+        level = l;
       }
+    };
+    for (int l = kFew ? wave : 0; l < lv.count; l += kFew ? waves : 1) {
+      const uint32_t p = octet_bound<!kFew, false, false>(lv, top, l, k, kq, nullptr);
+      cur[l * kStride] = p;
+      const uint32_t key = p > 0u ? lv.v[l].kv[p - 1u] >> 1 : 0u;
+      if (kFew) elem[l * kStride] = key;
+      else take(l, p, key);
+    }
+    if constexpr (kFew) {
+      __syncthreads();
+      if (wave != 0) return;  // one block of queries a work-group
+      for (int l = 0; l < lv.count; ++l) take(l, cur[l * kStride], elem[l * kStride]);
     }
     uint32_t at = 0u;
     while (best != kNoKey) {
-      at = run_start(lv, level, cur[level * kQueryThreads] - 1u, best);
+      at = run_start(lv, level, cur[level * kStride] - 1u, best);
       if ((as_global(lv.v[level].kv)[at] & 1u) != 0u) break;
       const uint32_t gone = best;
       best = kNoKey;
       for (int l = 0; l < lv.count; ++l) {
-        uint32_t p = cur[l * kQueryThreads];
+        uint32_t p = cur[l * kStride];
         if (p == 0u) continue;
         uint32_t key = lv.v[l].kv[p - 1u] >> 1;
         if (key == gone) {
           p = run_start(lv, l, p - 1u, gone);
-          cur[l * kQueryThreads] = p;
+          cur[l * kStride] = p;
           if (p == 0u) continue;
           key = lv.v[l].kv[p - 1u] >> 1;
         }
-        if (best == kNoKey || key > best) {
-          best = key;
-          level = l;
-        }
+        take(l, p, key);
       }
     }
     if (i < nq) {
@@ -3716,25 +3840,31 @@ hipError_t launch_fill_runs(uint32_t* a_kv, uint32_t* a_val, uint32_t* b_kv, uin
 }
 
 // Levels with their tops, and the grid of a query kernel that strides over the
-// queries.  Up to kFewQueries the work-groups run side by side and loading the
-// tops would be part of every query's latency: 100 lookups on one, three and
-// five levels take 8.4, 15.7 and 24.6 us without them, 8.7, 18.2 and 26.2
-// with 8 KB of them.  Above, the grid is as large as keeps the loading of the
-// tops small beside the queries (with one level 2^22 lookups take 212 us in 4096
-// work-groups, 222 in 1280).
-constexpr uint32_t kFewQueries = 1u << 16;
+// queries.  Up to kFewQueries the work-groups run side by side: a query's
+// latency bounds the launch, so several levels are dealt to the waves of a
+// work-group (k_lookup_few and the like) and the tops, whose loading would be
+// part of every query's latency, are not used.  The two ways cross between
+// 2^17 and 2^18 queries: lookups on ten levels take 60 us dealt and 69 with
+// tops at 2^17, 111 and 96 at 2^18; counts 80 and 118, 143 and 163.  Order
+// queries, whose first wave works on alone, cross at half of that: successors
+// on seven levels 45 and 60 at 2^16, 73 and 71 at 2^17.  Above, the grid is as large as keeps the
+// loading of the tops small beside the queries (with one level 2^22 lookups
+// take 212 us in 4096 work-groups, 222 in 1280).  Where nothing is dealt (one
+// level counted, emission that searches) tops pay from half of kFewQueries on:
+// 2^17 counts on one level take 21.6 us with them, 23.1 without.
+constexpr uint32_t kFewQueries = 1u << 17;
 static QLevels query_levels_for(const LevelSet& lv, uint32_t nq) {
-  return query_levels(lv, nq <= kFewQueries ? 0u : kTopWords);
+  return query_levels(lv, nq <= kFewQueries / 2 ? 0u : kTopWords);
 }
 static unsigned query_grid(const QLevels& q, uint64_t nq, uint32_t per = 8) {
   const uint64_t block = kQueryThreads / 8 * per, g = (nq + block - 1) / block;
   const uint64_t most = 5u * 256u * (8192u / (q.words > 2048u ? q.words : 2048u));
   return static_cast<unsigned>(g < most ? g : most);
 }
-// Queries per octet of the several-level walks: eight, one after another, when
-// that leaves 2048 waves or more (8 on each of 256 CUs), else fewer, down to
-// one: 26 000 ranges of 32 keys on three levels take 91 us one at a time, 256
-// eight; 60 000 counts on ten levels 92 us by two, 144 by one.
+// Queries per octet of the several-level walks that do not share cursors: eight,
+// one after another, when that leaves 2048 waves or more (8 on each of 256 CUs),
+// else fewer, down to one: the emission of 26 000 ranges on three levels and
+// counts of 60 000 on ten (92 us by two, 144 by one) set the line there.
 static uint32_t queries_per_octet(uint32_t nq) {
   uint32_t per = 8;
   while (per > 1 && nq / (8u * per) < 2048u) per /= 2;
@@ -3748,8 +3878,11 @@ static unsigned walk_lds_words(const QLevels& q, bool emit) {
 hipError_t launch_lookup(const LevelSet& lv, const uint32_t* q, uint32_t nq, uint32_t* out_val,
                          uint8_t* out_found, hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
-  const QLevels ql = query_levels_for(lv, nq);
-  return launch_lds(ql.words != 0 ? k_lookup<true> : k_lookup<false>, query_grid(ql, nq), kQueryThreads, ql.words * 4u, stream, t, ql, q,
+  if (nq <= kFewQueries)
+    return launch(k_lookup_few, grid_for(nq, 64), 64 * few_waves(lv.count), stream, t,
+                  query_levels(lv, 0), q, nq, out_val, out_found);
+  const QLevels ql = query_levels(lv, kTopWords);
+  return launch_lds(k_lookup, query_grid(ql, nq), kQueryThreads, ql.words * 4u, stream, t, ql, q,
                     nq, out_val, out_found);
 }
 
@@ -3757,10 +3890,17 @@ hipError_t launch_count(const LevelSet& lv, const uint32_t* lo, const uint32_t* 
                         uint32_t* counts, uint64_t* scan_status, size_t scan_words,
                         uint32_t* bounds, hipStream_t stream, const KTimer* t) {
   if (nq == 0) return hipSuccess;
-    const QLevels ql = query_levels_for(lv, nq);
+  if (lv.count > 1 && nq <= kFewQueries) {
+    const uint32_t L = static_cast<uint32_t>(lv.count);
+    return launch_lds(k_count_few, grid_for(nq, 64), 64 * kFewWaves,
+                      (64u * L + 8u * kFewWaves * walk_list(L)) * 4u, stream, t,
+                      query_levels(lv, 0), lo, hi, nq, counts, scan_status,
+                      static_cast<uint64_t>(scan_words), bounds);
+  }
+  const QLevels ql = query_levels_for(lv, nq);
   const bool top = ql.words != 0;
   auto k = lv.count <= 1 ? (top ? k_count<true, false> : k_count<false, false>)
-                         : (top ? k_count<true, true> : k_count<false, true>);
+                         : k_count<true, true>;
   const unsigned lds = (ql.words + walk_lds_words(ql, false)) * 4u;
   const uint32_t per = lv.count <= 1 ? 8u : queries_per_octet(nq);
   return launch_lds(k, query_grid(ql, nq, per), kQueryThreads, lds, stream, t, ql, lo, hi, nq, per,
@@ -3777,24 +3917,32 @@ hipError_t launch_scan(const uint32_t* counts, uint32_t nq, uint64_t* offsets,
                 scan_status, fault);
 }
 
+template <typename Kernel>
+static hipError_t launch_order(Kernel many, Kernel few, const LevelSet& lv, const uint32_t* q,
+                               uint32_t nq, uint32_t* out_key, uint32_t* out_val,
+                               uint8_t* out_found, hipStream_t stream, const KTimer* t) {
+  if (nq == 0) return hipSuccess;
+  const unsigned L = static_cast<unsigned>(lv.count);
+  if (nq <= kFewQueries / 2)
+    return launch_lds(few, grid_for(nq, 64), 64 * few_waves(lv.count), 2u * 64u * L * 4u, stream,
+                      t, query_levels(lv, 0), q, nq, out_key, out_val, out_found);
+  const QLevels ql = query_levels(lv, kTopWords);
+  return launch_lds(many, query_grid(ql, nq), kQueryThreads, (ql.words + L * kQueryThreads) * 4u,
+                    stream, t, ql, q, nq, out_key, out_val, out_found);
+}
+
 hipError_t launch_successor(const LevelSet& lv, const uint32_t* q, uint32_t nq, uint32_t* out_key,
                             uint32_t* out_val, uint8_t* out_found, hipStream_t stream,
                             const KTimer* t) {
-  if (nq == 0) return hipSuccess;
-  const QLevels ql = query_levels_for(lv, nq);
-  const unsigned lds = (ql.words + static_cast<unsigned>(ql.count) * kQueryThreads) * 4u;
-  return launch_lds(ql.words != 0 ? k_successor<true> : k_successor<false>, query_grid(ql, nq), kQueryThreads, lds, stream, t, ql, q, nq,
-                    out_key, out_val, out_found);
+  return launch_order(k_successor<false>, k_successor<true>, lv, q, nq, out_key, out_val, out_found,
+                      stream, t);
 }
 
 hipError_t launch_predecessor(const LevelSet& lv, const uint32_t* q, uint32_t nq,
                               uint32_t* out_key, uint32_t* out_val, uint8_t* out_found,
                               hipStream_t stream, const KTimer* t) {
-  if (nq == 0) return hipSuccess;
-  const QLevels ql = query_levels_for(lv, nq);
-  const unsigned lds = (ql.words + static_cast<unsigned>(ql.count) * kQueryThreads) * 4u;
-  return launch_lds(ql.words != 0 ? k_predecessor<true> : k_predecessor<false>, query_grid(ql, nq), kQueryThreads, lds, stream, t, ql, q, nq,
-                    out_key, out_val, out_found);
+  return launch_order(k_predecessor<false>, k_predecessor<true>, lv, q, nq, out_key, out_val,
+                      out_found, stream, t);
 }
 
 uint32_t clean_tiles(uint32_t n) { return grid_for(n, kCleanTile); }

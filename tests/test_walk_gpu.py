@@ -46,7 +46,8 @@ def test_tree_sizes(b, R, domain):
 
 @pytest.mark.parametrize("nq", [1, 100, 40000, 70000, 140000])
 def test_queries_per_octet(nq):
-    """1, 2, 4 and 8 queries an octet, against numpy on the live pairs."""
+    """1, 2, 4 and 8 queries an octet, and both sides of the number of queries up
+    to which the levels are dealt to the waves, against numpy on the live pairs."""
     note("queries per octet nq=%d" % nq)
     rng = np.random.default_rng(nq)
     b = 3000
@@ -66,6 +67,7 @@ def test_queries_per_octet(nq):
     want = np.concatenate([live[x:y] for x, y in zip(a, e)] + [live[:0]])
     assert np.array_equal(host(keys), want)
     assert np.array_equal(host(vals), t.m.lookup(want.astype(np.uint32))[0])
+    check(t, lo, lo[:100], hi[:100])
     t.g.close()
 
 
