@@ -131,7 +131,7 @@ struct SortMeta {
 // work-group at little more than a copy, so the first path is the faster one
 // as long as the largest bucket holds at most kMsdMaxBucket elements: Zipf(1.1)
 // keys whose first takes 8 % of a batch need 18 us a batch of 2^15 (2700 in its
-// bucket; 42 by digit passes), 45 of 2^17 (10 800; 56) and 157 of 2^19 (43 000;
+// bucket; 42 by digit passes), 40 of 2^17 (10 800; 56) and 157 of 2^19 (43 000;
 // 87).  Each sort records its largest top-digit bucket so that the next sort
 // can pick the path; one above kLocalCap that is not due to one key (or may not
 // be: a digit pass cannot tell) counts as above kMsdMaxBucket.
