@@ -3037,6 +3037,55 @@ __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
   }
 }
 
+// Emission of up to kNarrow pairs a query over at most kNarrowLevels levels: a
+// lane walks its own query, one key at a time, the levels' next elements in
+// registers.  Writes pairs [o, z) of the query from the cursors in cur; gives up
+// after kNarrowKeys keys (many of them deleted).  Returns whether every lane of
+// the wave has written all its pairs; writing them again is harmless.  Octets
+// need a round for each of a wave's queries, however few pairs it has: 2^20
+// ranges of one key on three levels take 139 us by octets and 43 so, of two 147
+// and 72, on five levels 162 and 60; with eight keys both take 225.
+constexpr uint32_t kNarrow = 8, kNarrowLevels = 6, kNarrowKeys = 20;
+__device__ __forceinline__ bool emit_narrow(const QLevels& lv, const uint32_t* cur, uint32_t k2,
+                                            uint64_t o, uint64_t z, uint32_t* out_keys,
+                                            uint32_t* out_vals) {
+  uint32_t c[kNarrowLevels], x[kNarrowLevels];
+  const uint32_t h = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
+#pragma unroll
+  for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
+    const bool on = l < lv.count && o < z;
+    c[l] = on ? cur[l * 64] : 0u;
+    x[l] = on && c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : kNoKey;
+  }
+  for (uint32_t step = 0; step < kNarrowKeys && ballot(o < z) != 0; ++step) {
+    uint32_t best = kNoKey, y = 0u, at = 0u;  // the smallest key and its newest instance
+    const uint32_t* val = nullptr;
+#pragma unroll
+    for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
+      if (x[l] <= h && (x[l] >> 1) < best) {
+        best = x[l] >> 1;
+        y = x[l];
+        at = c[l];
+        val = lv.v[l].val;
+      }
+    }
+    if (best == kNoKey) break;  // only after a timed-out scan
+    if (o < z && (y & 1u) != 0u) {
+      out_keys[o] = best;
+      out_vals[o] = as_global(val)[at];
+      ++o;
+    }
+#pragma unroll
+    for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
+      if (o < z && (x[l] >> 1) == best && x[l] != kNoKey) {
+        c[l] = skip_run(lv.v[l].kv, c[l], lv.v[l].len, best);
+        x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : kNoKey;
+      }
+    }
+  }
+  return ballot(o < z) == 0;
+}
+
 // Stage 3 of sec. IV-C / IV-D over several levels.  An octet writes its
 // query's pairs at the query's offset, chunk by chunk: a valid entry's place is
 // the number of valid entries of the chunk with a smaller key.  A query whose
@@ -3084,6 +3133,11 @@ __global__ __launch_bounds__(kQueryThreads) void k_range_emit(QLevels lv,
     }
     wave_sync();
     const uint32_t h2 = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
+    if (!kSearch && per == 8 && L <= kNarrowLevels && ballot(z - o > kNarrow) == 0 &&
+        emit_narrow(lv, w.cur + lane, k2, o, z, out_keys, out_vals)) {
+      wave_sync();
+      continue;
+    }
     for (uint32_t r = 0; r < per; ++r) {
       const int qi = static_cast<int>((lane & 56u) + r);
       const uint32_t h = static_cast<uint32_t>(__shfl(static_cast<int>(h2), qi, 64));

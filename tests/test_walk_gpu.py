@@ -92,3 +92,33 @@ def test_runs_across_chunks(run):
     hi = lo + np.tile([0, 1, 4, 150], 115)
     check(t, np.arange(890, 1110), lo, hi)
     t.g.close()
+
+
+@pytest.mark.parametrize("R", [2, 3, 7, 21, 63, 127])
+def test_narrow_ranges(R):
+    """Ranges of few pairs, many queries: widths around the number of pairs up to
+    which a lane walks its own query, blocks of more deleted keys than it passes
+    over, up to seven levels (six are walked so), against numpy on the live pairs."""
+    note("narrow ranges R=%d" % R)
+    rng = np.random.default_rng(R)
+    b, top = 400, 6000
+    t = Trio(b)
+    for i in range(R):
+        if i % 3 == 2:
+            t.delete((int(rng.integers(0, top - b)) + np.arange(b if i % 2 else 30)).astype(np.uint32))
+        else:
+            t.insert(*batch(rng, b, top))
+    live = np.nonzero(t.m.lookup(np.arange(top, dtype=np.uint32))[1])[0].astype(np.int64)
+    nq = 140001
+    lo = rng.integers(0, top, nq)
+    lo[nq // 2:] = np.sort(lo[nq // 2:])
+    density = max(1, len(live)) / top
+    hi = lo + rng.integers(0, int(9 / density) + 2, nq) * (rng.random(nq) < 0.7)
+    a, e = np.searchsorted(live, lo), np.searchsorted(live, hi, side="right")
+    off, keys, vals = t.g.range(dev(lo), dev(hi), cap=int((e - a).sum()))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(off).astype(np.int64), np.r_[0, np.cumsum(e - a)])
+    want = np.concatenate([live[x:y] for x, y in zip(a, e)] + [live[:0]])
+    assert np.array_equal(host(keys), want)
+    assert np.array_equal(host(vals), t.m.lookup(want.astype(np.uint32))[0])
+    t.g.close()
