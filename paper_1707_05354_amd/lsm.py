@@ -45,7 +45,11 @@ KERNEL_NAMES = ("k_sort_hist", "k_sort_pass", "k_merge", "k_lookup", "k_count", 
                 "k_range_emit", "k_order", "k_clean", "(unused)", "k_msd_scatter",
                 "k_local_sort", "k_sort_step")
 # rocprofv3 kernel names behind each profiler kind that covers several kernels.
-KERNEL_TRACE_NAMES = {"k_order": ("k_successor", "k_predecessor"),
+KERNEL_TRACE_NAMES = {"k_lookup": ("k_lookup", "k_lookup_few"),
+                      "k_count": ("k_count<false, false>", "k_count<true, false>", "k_count<true, true>",
+                                  "k_count_few"),
+                      "k_order": ("k_successor<false>", "k_successor<true>", "k_predecessor<false>",
+                                  "k_predecessor<true>"),
                       "k_clean": ("k_clean_count", "k_clean_scatter", "k_clean_pad"),
                       "k_merge": ("k_merge<4>", "k_merge<8>", "k_merge<16>"),
                       "k_local_sort": ("k_local_sort<false>", "k_local_sort<true>"),
