@@ -3039,12 +3039,15 @@ __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
 
 // Emission of up to kNarrow pairs a query over at most kNarrowLevels levels: a
 // lane walks its own query, one key at a time, the levels' next elements in
-// registers.  Writes pairs [o, z) of the query from the cursors in cur; gives up
-// after kNarrowKeys keys (many of them deleted).  Returns whether every lane of
-// the wave has written all its pairs; writing them again is harmless.  Octets
-// need a round for each of a wave's queries, however few pairs it has: 2^20
-// ranges of one key on three levels take 139 us by octets and 43 so, of two 147
-// and 72, on five levels 162 and 60; with eight keys both take 225.
+// registers.  A level has one while its cursor is below its length: every 32-bit
+// word is the key variable of some element (all ones that of key 2^31 - 1), so
+// no word can stand for none.  Writes pairs [o, z) of the query from the cursors
+// in cur; gives up after kNarrowKeys keys (many of them deleted).  Returns
+// whether every lane of the wave has written all its pairs; writing them again
+// is harmless.  Octets need a round for each of a wave's queries, however few
+// pairs it has: 2^20 ranges of one key on three levels take 139 us by octets and
+// 43 so, of two 147 and 72, on five levels 162 and 60; with eight keys both take
+// 225.
 constexpr uint32_t kNarrow = 8, kNarrowLevels = 6, kNarrowKeys = 20;
 __device__ __forceinline__ bool emit_narrow(const QLevels& lv, const uint32_t* cur, uint32_t k2,
                                             uint64_t o, uint64_t z, uint32_t* out_keys,
@@ -3053,16 +3056,15 @@ __device__ __forceinline__ bool emit_narrow(const QLevels& lv, const uint32_t* c
   const uint32_t h = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
 #pragma unroll
   for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
-    const bool on = l < lv.count && o < z;
-    c[l] = on ? cur[l * 64] : 0u;
-    x[l] = on && c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : kNoKey;
+    c[l] = l < lv.count && o < z ? cur[l * 64] : lv.v[l].len;  // levels past the last: 0
+    x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
   }
   for (uint32_t step = 0; step < kNarrowKeys && ballot(o < z) != 0; ++step) {
     uint32_t best = kNoKey, y = 0u, at = 0u;  // the smallest key and its newest instance
     const uint32_t* val = nullptr;
 #pragma unroll
     for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
-      if (x[l] <= h && (x[l] >> 1) < best) {
+      if (c[l] < lv.v[l].len && x[l] <= h && (x[l] >> 1) < best) {
         best = x[l] >> 1;
         y = x[l];
         at = c[l];
@@ -3077,9 +3079,9 @@ __device__ __forceinline__ bool emit_narrow(const QLevels& lv, const uint32_t* c
     }
 #pragma unroll
     for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
-      if (o < z && (x[l] >> 1) == best && x[l] != kNoKey) {
+      if (o < z && c[l] < lv.v[l].len && (x[l] >> 1) == best) {
         c[l] = skip_run(lv.v[l].kv, c[l], lv.v[l].len, best);
-        x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : kNoKey;
+        x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
       }
     }
   }
