@@ -906,10 +906,10 @@ lsm_status_t update_batch(lsm_t h, const uint32_t* keys, const uint32_t* vals,
   }
   int launched = 0;
   const hipError_t se = launch_sort(sa, h->stream, timed ? sort_t : nullptr, &launched);
-  // The digit-pass sort's first kernel clears the other histogram buffer for
-  // the next such sort; once it has been launched, the next one must use
-  // that buffer whether or not the rest of the sort was launched.
-  if (sa.path == kSortLsd && launched > 0) h->hist_parity ^= 1;
+  // The first kernel of a sort that uses the histogram clears the other
+  // buffer for the next such sort; once it has been launched, the next one must
+  // use that buffer whether or not the rest of the sort was launched.
+  if (sort_uses_hist(sa) && launched > 0) h->hist_parity ^= 1;
   if (se != hipSuccess) return LSM_EHIP;
   Timed last = st[nk - 1];
   bool indexed = false;
@@ -1284,7 +1284,7 @@ lsm_status_t lsm_bulk_insert(lsm_t h, const uint32_t* d_keys, const uint32_t* d_
     }
     int launched = 0;
     e = launch_sort(sa, h->stream, timed ? tt : nullptr, &launched);
-    if (sa.path == kSortLsd && launched > 0) parity ^= 1;  // see update_batch
+    if (sort_uses_hist(sa) && launched > 0) parity ^= 1;  // see update_batch
     sorted += len;
     const uint32_t* ak = sa.out_kv;
     const uint32_t* av = sa.out_val;

@@ -102,9 +102,9 @@ struct BatchSrc {
 };
 
 // Sort scratch layout (uint32 words) for a batch of b elements.  The global
-// digit histogram of the digit-pass sort is double-buffered: a sort
-// accumulates into hist[parity] and clears hist[parity ^ 1] for the next one
-// (both start zeroed).  The top-digit sort has kMaxGroup + 1 slots, so that
+// digit histogram of the digit-pass sort is double-buffered: a sort that uses
+// it (sort_uses_hist) accumulates into hist[parity] and clears hist[parity ^ 1]
+// for the next one (both start zeroed).  The top-digit sort has kMaxGroup + 1 slots, so that
 // one batch can be scattered while the buckets of up to kMaxGroup earlier
 // batches (a group sorted together) are sorted: each slot holds a scattered
 // batch, the tiles' digit-group starts and the slot's largest-bucket record.
@@ -244,6 +244,14 @@ struct LevelDst {
   uint64_t len[kMaxLevels];
   int count;
 };
+
+// Whether a sort goes through the global digit histogram: adds to hist[parity]
+// and clears hist[parity ^ 1], so that the next one has to take the other
+// parity.  Sorts above kMsdMaxTiles tiles keep their counts elsewhere and touch
+// neither buffer.
+inline bool sort_uses_hist(const SortArgs& a) {
+  return a.path == kSortLsd && a.meta.num_sort_tiles <= static_cast<uint32_t>(kMsdMaxTiles);
+}
 
 size_t sort_meta_words(uint32_t b);
 SortMeta sort_meta_carve(uint32_t* base, uint32_t b, int parity, int slot);
