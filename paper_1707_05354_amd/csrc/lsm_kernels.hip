@@ -1744,6 +1744,8 @@ __device__ __forceinline__ void merge_large(LocalLds& L, int R, Out out) {
       if (tid < static_cast<uint32_t>(R)) L.cur[tid] += L.cut[tid];
     } else {
       // The runs of key B (a run that does not start with it has none here).
+      // Their lengths go to L.cut, which every wave has to have summed first.
+      __syncthreads();
       for (int r = static_cast<int>(wave); r < R; r += kWaves) {
         const uint32_t e = wave_upper(L.run_k[r], L.cur[r], L.len[r], B);
         if ((tid & 63u) == 0) L.cut[r] = e - L.cur[r];
