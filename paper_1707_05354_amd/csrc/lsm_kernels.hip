@@ -2735,13 +2735,19 @@ struct WalkLds {
 };
 // List entries of an octet: a multiple of 4 words (16-byte reads), an odd one,
 // so that the octets' lists start on different LDS banks.
-__host__ __device__ inline uint32_t walk_list(uint32_t levels) {
+__host__ __device__ constexpr uint32_t walk_list(uint32_t levels) {
   const uint32_t quads = 2 * levels + 4;  // 8 entries a level, 16 of two
   return 4u * (quads | 1u);
 }
-__host__ __device__ inline uint32_t walk_words(uint32_t levels, bool emit) {
+__host__ __device__ constexpr uint32_t walk_words(uint32_t levels, bool emit) {
   return 64u * levels + 8u * walk_list(levels) * (emit ? 2u : 1u);
 }
+// A work-group can have the 160 KB of its CU; with 32 levels the emission that
+// searches takes 117 (64 KB from 20 levels on without tops, from 15 with them).
+constexpr uint32_t kLdsBytes = 160 * 1024;
+static_assert(4u * (kTopWords + kQueryWaves * walk_words(kMaxLevels, true)) <= kLdsBytes &&
+                  4u * (64u * kMaxLevels + 8u * kFewWaves * walk_list(kMaxLevels)) <= kLdsBytes,
+              "every number of levels fits");
 __device__ __forceinline__ WalkLds walk_lds(uint32_t* wave_lds, uint32_t levels, bool emit) {
   const uint32_t octet = lane_id() >> 3, len = walk_list(levels);
   WalkLds w;
