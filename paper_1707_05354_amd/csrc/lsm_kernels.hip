@@ -2981,15 +2981,118 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_count_few(QLevels lv, const 
   }
 }
 
+// Queries of few candidates over at most kN levels: a lane walks its own query,
+// a step for every key, the levels' next elements in registers.  A level has an
+// element while its cursor is below its length: every 32-bit word is the key
+// variable of some element (all ones that of key 2^31 - 1), so no word can stand
+// for none.  (Octets need a round for each of a wave's queries, however few
+// candidates it has.)
+constexpr int kNarrowLevels = 10;
+constexpr uint32_t kNarrowSteps = 40;
+template <int kN>
+struct NarrowWalk {
+  uint32_t c[kN], x[kN];
+  uint32_t key, last;  // the step's key, and that of the step before
+  uint32_t elem, at;   // the key's newest element and its place
+  const uint32_t* val;
+
+  // From the cursors in cur (word 64 l for level l); on: the lane has a query.
+  __device__ __forceinline__ void start(const QLevels& lv, const uint32_t* cur, bool on) {
+    key = kNoKey;
+#pragma unroll
+    for (int l = 0; l < kN; ++l)  // (levels past the last have length 0)
+      c[l] = l < lv.count && on ? cur[l * 64] : lv.v[l].len;
+#pragma unroll
+    for (int l = 0; l < kN; ++l) x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
+  }
+  // The smallest key; false when there is none up to kv word h.
+  __device__ __forceinline__ bool next(const QLevels& lv, uint32_t h) {
+    last = key;
+    key = kNoKey;
+    elem = at = 0u;
+    val = nullptr;
+#pragma unroll
+    for (int l = 0; l < kN; ++l) {
+      if (c[l] < lv.v[l].len && x[l] <= h && (x[l] >> 1) < key) {  // ties: the newer level's stays
+        key = x[l] >> 1;
+        elem = x[l];
+        at = c[l];
+        val = lv.v[l].val;
+      }
+    }
+    return key != kNoKey;
+  }
+  // Whether `elem` is a live pair: a regular element and not an older one of the
+  // key of the step before.
+  __device__ __forceinline__ bool live() const { return key != last && (elem & 1u) != 0u; }
+  // Past one element of the key in every level that has it.
+  __device__ __forceinline__ void pass(const QLevels& lv) {
+#pragma unroll
+    for (int l = 0; l < kN; ++l) {
+      if (c[l] < lv.v[l].len && (x[l] >> 1) == key) {
+        ++c[l];
+        x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
+      }
+    }
+  }
+};
+
+// Counts the wave's queries lane by lane.  False, with nothing counted, when some
+// lane's query has more than `far` candidates in the largest level (the last) or
+// takes more than kNarrowSteps steps.
+template <int kN>
+__device__ __forceinline__ bool count_narrow(const QLevels& lv, const uint32_t* cur, uint32_t h,
+                                             uint32_t far, uint32_t* count) {
+  const QLevel& last = lv.v[lv.count - 1];
+  const uint32_t c = cur[(lv.count - 1) * 64];
+  const bool reaches = c < last.len && last.len - c > far;
+  const uint32_t z = reaches ? last.kv[c + far] : 0u;
+  if (ballot(reaches && z <= h) != 0) return false;
+  NarrowWalk<kN> w;
+  w.start(lv, cur, true);
+  uint32_t n = 0;
+  bool more = true;
+  for (uint32_t i = 0; i < kNarrowSteps && ballot(more) != 0; ++i) {
+    more = w.next(lv, h);
+    n += more && w.live() ? 1u : 0u;
+    w.pass(lv);  // (no level has kNoKey)
+  }
+  *count = n;
+  return ballot(more) == 0;
+}
+
+// Writes pairs [o, z) of the lane's query from the cursors in cur; gives up after
+// kNarrowSteps steps (many deleted keys or long runs).  Returns whether every lane
+// of the wave has written all its pairs; writing them again is harmless.
+template <int kN>
+__device__ __forceinline__ bool emit_narrow(const QLevels& lv, const uint32_t* cur, uint32_t k2,
+                                            uint64_t o, uint64_t z, uint32_t* out_keys,
+                                            uint32_t* out_vals) {
+  const uint32_t h = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
+  NarrowWalk<kN> w;
+  w.start(lv, cur, o < z);
+  for (uint32_t i = 0; i < kNarrowSteps && ballot(o < z) != 0; ++i) {
+    if (!w.next(lv, h)) break;  // no query, or only after a timed-out scan
+    if (o < z && w.live()) {
+      out_keys[o] = w.key;
+      out_vals[o] = as_global(w.val)[w.at];
+      ++o;
+    }
+    if (o < z) w.pass(lv);
+  }
+  return ballot(o < z) == 0;
+}
+
 // Count pass.  With bounds non-null, each query's position in the levels is
 // stored for the emission pass: with one level its candidate bounds
 // [lower_bound(lo), upper_bound(hi)) (two words per query), with several its
 // cursors (lower bounds), level-major (word l * nq + query).
-// kMany: several occupied levels.
-template <bool kTop, bool kMany>
+// kMany: several occupied levels; kN != 0: waves of few candidates (`far`) count
+// lane by lane.
+template <bool kTop, bool kMany, int kN>
 __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
                                                          const uint32_t* lo, const uint32_t* hi,
-                                                         uint32_t nq, uint32_t per,
+                                                         uint32_t nq, uint32_t far,
                                                          uint32_t* counts, uint64_t* scan_status,
                                                          uint64_t scan_words, uint32_t* bounds) {
   extern __shared__ uint32_t top[];
@@ -3002,14 +3105,13 @@ __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
   const uint32_t L = static_cast<uint32_t>(lv.count);
   WalkLds w{};
   if (kMany) w = walk_lds(top + lv.words + wave * walk_words(L, false), L, false);
-  const uint32_t block = kQueryThreads / 8 * per, slot = query_slot(per);
-  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * block; q0 < nq;
-       q0 += static_cast<uint64_t>(gridDim.x) * block) {
+  for (uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kQueryThreads; q0 < nq;
+       q0 += static_cast<uint64_t>(gridDim.x) * kQueryThreads) {
     // Every lane takes part in the wave-wide descents; lanes without a query
     // search the empty range [1, 0].
-    const uint64_t gi = q0 + slot;
-    const bool active = sub < per && gi < nq;
-    const uint32_t k1 = gi < nq ? lo[gi] : 1u, k2 = gi < nq ? hi[gi] : 0u;
+    const uint64_t gi = q0 + threadIdx.x;
+    const bool active = gi < nq;
+    const uint32_t k1 = active ? lo[gi] : 1u, k2 = active ? hi[gi] : 0u;
     uint32_t kq[8];
     octet_lanes(k1, kq);
     if constexpr (!kMany) {
@@ -3033,7 +3135,14 @@ __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
       wave_sync();
       const uint32_t h2 = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
       uint32_t res = 0;
-      for (uint32_t r = 0; r < per; ++r) {
+      bool narrow = false;
+      if constexpr (kN != 0) narrow = count_narrow<kN>(lv, w.cur + lane, h2, far, &res);
+      if (narrow) {
+        wave_sync();
+        if (active) counts[gi] = res;
+        continue;
+      }
+      for (uint32_t r = 0; r < 8; ++r) {
         const uint32_t qi = (lane & 56u) + r;
         const uint32_t h =
             static_cast<uint32_t>(__shfl(static_cast<int>(h2), static_cast<int>(qi), 64));
@@ -3045,69 +3154,21 @@ __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
   }
 }
 
-// Emission of up to kNarrow pairs a query over at most kNarrowLevels levels: a
-// lane walks its own query, one key at a time, the levels' next elements in
-// registers.  A level has one while its cursor is below its length: every 32-bit
-// word is the key variable of some element (all ones that of key 2^31 - 1), so
-// no word can stand for none.  Writes pairs [o, z) of the query from the cursors
-// in cur; gives up after kNarrowKeys keys (many of them deleted).  Returns
-// whether every lane of the wave has written all its pairs; writing them again
-// is harmless.  Octets need a round for each of a wave's queries, however few
-// pairs it has: 2^20 ranges of one key on three levels take 139 us by octets and
-// 43 so, of two 147 and 72, on five levels 162 and 60; with eight keys both take
-// 225.
-constexpr uint32_t kNarrow = 8, kNarrowLevels = 6, kNarrowKeys = 20;
-__device__ __forceinline__ bool emit_narrow(const QLevels& lv, const uint32_t* cur, uint32_t k2,
-                                            uint64_t o, uint64_t z, uint32_t* out_keys,
-                                            uint32_t* out_vals) {
-  uint32_t c[kNarrowLevels], x[kNarrowLevels];
-  const uint32_t h = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
-#pragma unroll
-  for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
-    c[l] = l < lv.count && o < z ? cur[l * 64] : lv.v[l].len;  // levels past the last: 0
-    x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
-  }
-  for (uint32_t step = 0; step < kNarrowKeys && ballot(o < z) != 0; ++step) {
-    uint32_t best = kNoKey, y = 0u, at = 0u;  // the smallest key and its newest instance
-    const uint32_t* val = nullptr;
-#pragma unroll
-    for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
-      if (c[l] < lv.v[l].len && x[l] <= h && (x[l] >> 1) < best) {
-        best = x[l] >> 1;
-        y = x[l];
-        at = c[l];
-        val = lv.v[l].val;
-      }
-    }
-    if (best == kNoKey) break;  // only after a timed-out scan
-    if (o < z && (y & 1u) != 0u) {
-      out_keys[o] = best;
-      out_vals[o] = as_global(val)[at];
-      ++o;
-    }
-#pragma unroll
-    for (int l = 0; l < static_cast<int>(kNarrowLevels); ++l) {
-      if (o < z && c[l] < lv.v[l].len && (x[l] >> 1) == best) {
-        c[l] = skip_run(lv.v[l].kv, c[l], lv.v[l].len, best);
-        x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
-      }
-    }
-  }
-  return ballot(o < z) == 0;
-}
-
 // Stage 3 of sec. IV-C / IV-D over several levels.  An octet writes its
 // query's pairs at the query's offset, chunk by chunk: a valid entry's place is
 // the number of valid entries of the chunk with a smaller key.  A query whose
 // pairs would end beyond cap writes nothing (the caller sees
 // offsets[q + 1] > cap); writes stay inside [offsets[q], offsets[q + 1]) even
 // for offsets corrupted by a timed-out scan.  Cursors as the count pass stored
-// them, or, with kSearch, from descents.
-template <bool kTop, bool kSearch>
-__global__ __launch_bounds__(kQueryThreads) void k_range_emit(QLevels lv,
+// them, or, with kSearch, from descents.  kN != 0: waves whose queries all have at
+// most narrow_max pairs emit lane by lane.  (Without the bound of five waves a
+// SIMD the lane walk takes registers from the octets': 16 pairs a query on six
+// levels 345 us with it, 389 without.)
+template <bool kTop, bool kSearch, int kN>
+__global__ __launch_bounds__(kQueryThreads, kSearch ? 1 : 5) void k_range_emit(QLevels lv,
                                                               const uint32_t* lo,
                                                               const uint32_t* hi, uint32_t nq,
-                                                              uint32_t per,
+                                                              uint32_t per, uint32_t narrow_max,
                                                               const uint64_t* offsets,
                                                               const uint32_t* cursors,
                                                               uint32_t* out_keys,
@@ -3143,8 +3204,11 @@ __global__ __launch_bounds__(kQueryThreads) void k_range_emit(QLevels lv,
     }
     wave_sync();
     const uint32_t h2 = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
-    if (!kSearch && per == 8 && L <= kNarrowLevels && ballot(z - o > kNarrow) == 0 &&
-        emit_narrow(lv, w.cur + lane, k2, o, z, out_keys, out_vals)) {
+    bool narrow = false;
+    if constexpr (kN != 0)
+      narrow = per == 8 && ballot(z - o > narrow_max) == 0 &&
+               emit_narrow<kN>(lv, w.cur + lane, k2, o, z, out_keys, out_vals);
+    if (narrow) {
       wave_sync();
       continue;
     }
@@ -3986,19 +4050,41 @@ constexpr uint32_t kFewQueries = 1u << 17;
 static QLevels query_levels_for(const LevelSet& lv, uint32_t nq) {
   return query_levels(lv, nq <= kFewQueries / 2 ? 0u : kTopWords);
 }
-static unsigned query_grid(const QLevels& q, uint64_t nq, uint32_t per = 8) {
-  const uint64_t block = kQueryThreads / 8 * per, g = (nq + block - 1) / block;
+static unsigned query_grid(const QLevels& q, uint64_t nq) {
+  const uint64_t g = (nq + kQueryThreads - 1) / kQueryThreads;
   const uint64_t most = 5u * 256u * (8192u / (q.words > 2048u ? q.words : 2048u));
   return static_cast<unsigned>(g < most ? g : most);
 }
-// Queries per octet of the several-level walks that do not share cursors: eight,
-// one after another, when that leaves 2048 waves or more (8 on each of 256 CUs),
-// else fewer, down to one: the emission of 26 000 ranges on three levels and
-// counts of 60 000 on ten (92 us by two, 144 by one) set the line there.
+// Queries per octet of the several-level emission: eight, one after another, when
+// that leaves 2048 waves or more (8 on each of 256 CUs), else fewer, down to one:
+// the emission of 26 000 ranges on three levels set the line there.
 static uint32_t queries_per_octet(uint32_t nq) {
   uint32_t per = 8;
   while (per > 1 && nq / (8u * per) < 2048u) per /= 2;
   return per;
+}
+// When a lane walks its query alone: whether counts may, with at most `far`
+// candidates in the largest level, and up to how many pairs every query of a wave
+// may have in the emission (0: never).  An octet's load instruction reads eight
+// lines, a lane walk's 64, so the rule depends on where the levels lie (4 MB of L2
+// hold the keys of 2^20 elements).  Octets alone and with lane walks, us: 2^20
+// counts of one key on three levels of 0.7 M elements 156 and 81, of four keys 163
+// and 99, of 16 (octets both) 242 and 244; of one key on eight levels of 1 M 274
+// and 190, of eight 298 and 274; the ranges of these counts 221 and 139, 340 and
+// 251, 551 and 552, 477 and 273, 571 and 569.  On larger levels waves of both
+// kinds together cost more than either kind alone (2^18 counts of two keys on four
+// levels of 48 M 70 and 77), so counts stay with the octets there; the emission
+// knows its pairs and keeps to eight (2^20 ranges of one key on three levels of
+// 45 M 380 and 281), up to six levels.
+struct NarrowRule {
+  bool count;
+  uint32_t far, pairs;
+};
+static NarrowRule narrow_rule(const LevelSet& lv) {
+  uint64_t n = 0;
+  for (int l = 0; l < lv.count; ++l) n += lv.len[l];
+  if (lv.count > kNarrowLevels) return {false, 0, 0};
+  return n <= (1u << 21) ? NarrowRule{true, 11, 12} : NarrowRule{false, 0, lv.count <= 6 ? 8u : 0u};
 }
 // LDS words of the several-level walk of one work-group.
 static unsigned walk_lds_words(const QLevels& q, bool emit) {
@@ -4029,12 +4115,15 @@ hipError_t launch_count(const LevelSet& lv, const uint32_t* lo, const uint32_t* 
   }
   const QLevels ql = query_levels_for(lv, nq);
   const bool top = ql.words != 0;
-  auto k = lv.count <= 1 ? (top ? k_count<true, false> : k_count<false, false>)
-                         : k_count<true, true>;
+  const NarrowRule nr = narrow_rule(lv);
+  auto k = lv.count <= 1   ? (top ? k_count<true, false, 0> : k_count<false, false, 0>)
+           : !nr.count     ? k_count<true, true, 0>
+           : lv.count <= 3 ? k_count<true, true, 3>
+           : lv.count <= 6 ? k_count<true, true, 6>
+                           : k_count<true, true, kNarrowLevels>;
   const unsigned lds = (ql.words + walk_lds_words(ql, false)) * 4u;
-  const uint32_t per = lv.count <= 1 ? 8u : queries_per_octet(nq);
-  return launch_lds(k, query_grid(ql, nq, per), kQueryThreads, lds, stream, t, ql, lo, hi, nq, per,
-                    counts, scan_status, static_cast<uint64_t>(scan_words), bounds);
+  return launch_lds(k, query_grid(ql, nq), kQueryThreads, lds, stream, t, ql, lo, hi, nq,
+                    nr.far, counts, scan_status, static_cast<uint64_t>(scan_words), bounds);
 }
 
 size_t scan_status_words(uint32_t nq) { return 1 + grid_for(nq, kScanTile); }
@@ -4115,13 +4204,15 @@ hipError_t launch_range_emit(const LevelSet& lv, const uint32_t* lo, const uint3
                                         : k_range_emit_one<false, 4, true>,
                       grid, kQueryThreads, ql.words * 4u, stream, t, ql, lo, hi, nq, offsets,
                       bounds, out_keys, out_vals, cap);
-  auto k = bounds != nullptr ? k_range_emit<false, false>
-           : top             ? k_range_emit<true, true>
-                             : k_range_emit<false, true>;
+  const NarrowRule nr = narrow_rule(lv);
+  auto k = bounds == nullptr ? (top ? k_range_emit<true, true, 0> : k_range_emit<false, true, 0>)
+           : lv.count <= 3   ? k_range_emit<false, false, 3>
+           : lv.count <= 6   ? k_range_emit<false, false, 6>
+                             : k_range_emit<false, false, kNarrowLevels>;
   const unsigned lds = (ql.words + walk_lds_words(ql, true)) * 4u;
   const uint32_t per = queries_per_octet(nq);
   return launch_lds(k, grid_for(nq, kQueryThreads / 8 * per), kQueryThreads, lds, stream, t, ql,
-                    lo, hi, nq, per, offsets, bounds, out_keys, out_vals, cap);
+                    lo, hi, nq, per, nr.pairs, offsets, bounds, out_keys, out_vals, cap);
 }
 
 }  // namespace lsm

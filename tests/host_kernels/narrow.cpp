@@ -1,8 +1,9 @@
-// The emission's lane walk (emit_narrow) as one lane, on the CPU: dictionaries of
-// 1 to 6 levels with keys up to 2^31 - 1, every level in a heap array of its own
-// length, so that the sanitizer reports a read past its end.  Pairs against a
-// search of all levels.  (The walk's ballots only decide whether to go on for
-// another lane's sake, so one lane does what each of a wave's does.)
+// The lane walks of counts and emission (count_narrow, emit_narrow) as one lane, on
+// the CPU: dictionaries of 1 to 10 levels with keys up to 2^31 - 1, every level in a
+// heap array of its own length, so that the sanitizer reports a read past its end.
+// Counts and pairs against a search of all levels.  (The walks' ballots only
+// decide whether to go on for another lane's sake, so one lane does what each of
+// a wave's does.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,7 +26,7 @@ namespace lsm {
 int main() {
   using namespace lsm;
   std::mt19937 rng(1);
-  uint64_t checked = 0, top_emitted = 0;
+  uint64_t checked = 0, counted = 0, top_emitted = 0;
   for (int round = 0; round < 200000; ++round) {
     const int count = 1 + static_cast<int>(rng() % kNarrowLevels);
     std::vector<uint32_t*> kv(count), val(count);
@@ -61,8 +62,17 @@ int main() {
     for (int l = 0; l < count; ++l)
       while (cur[l * 64] < lv.v[l].len && (kv[l][cur[l * 64]] >> 1) < k1) ++cur[l * 64];
     std::vector<uint32_t> keys(want.size() + 2, 7u), vals(want.size() + 2, 7u);
-    if (want.size() <= kNarrow &&
-        emit_narrow(lv, cur.data(), k2, 1, 1 + want.size(), keys.data(), vals.data())) {
+    const uint32_t h = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
+    uint32_t n = 0;
+    const bool done = count <= 3 ? count_narrow<3>(lv, cur.data(), h, rng() % 8, &n)
+                                 : count_narrow<kNarrowLevels>(lv, cur.data(), h, rng() % 8, &n);
+    if (done && ++counted && n != want.size()) {
+      std::fprintf(stderr, "round %d: %u pairs counted, not %zu\n", round, n, want.size());
+      return 1;
+    }
+    if (count <= 6 && count > 3
+            ? emit_narrow<6>(lv, cur.data(), k2, 1, 1 + want.size(), keys.data(), vals.data())
+            : emit_narrow<kNarrowLevels>(lv, cur.data(), k2, 1, 1 + want.size(), keys.data(), vals.data())) {
       ++checked;
       for (size_t i = 0; i < want.size(); ++i) {
         if (keys[1 + i] != want[i].first || vals[1 + i] != want[i].second) {
@@ -79,7 +89,8 @@ int main() {
       delete[] val[l];
     }
   }
-  std::printf("narrow walk: ok, %llu walks, key 2^31 - 1 in %llu\n",
-              static_cast<unsigned long long>(checked), static_cast<unsigned long long>(top_emitted));
-  return checked > 100000 && top_emitted > 10000 ? 0 : 1;
+  std::printf("narrow walk: ok, %llu walks and %llu counts, key 2^31 - 1 in %llu\n",
+              static_cast<unsigned long long>(checked), static_cast<unsigned long long>(counted),
+              static_cast<unsigned long long>(top_emitted));
+  return checked > 100000 && counted > 100000 && top_emitted > 10000 ? 0 : 1;
 }
