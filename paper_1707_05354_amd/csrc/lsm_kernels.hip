@@ -676,6 +676,18 @@ __global__ __launch_bounds__(kThreads) void k_sort_hist(SortArgs a) {
     if (s_h[i] != 0u) atomicAdd(&mine[i], s_h[i]);
 }
 
+// Where element e < b of the batch, as the sort sees it (read back to front and
+// padded in front), stands in the caller's arrays.
+__device__ __forceinline__ uint32_t src_index(const BatchSrc& s, uint32_t e) {
+  const uint32_t x = s.b - 1 - e;
+  return x < s.n - 1 ? x : s.n - 1;
+}
+__device__ __forceinline__ uint32_t src_kv(const BatchSrc& s, uint32_t raw, uint32_t i) {
+  if (s.mode == kEncoded) return raw;
+  const uint32_t st = s.mode == kMixed ? (s.is_delete[i] ? 0u : 1u) : (s.mode == kDelete ? 0u : 1u);
+  return (raw << 1) | st;
+}
+
 // One stable counting pass of the batch sort on digit `pass`.  Tiles take
 // dynamic ids in start order (so every predecessor a tile waits for has
 // started); the tile a work-group most likely receives is loaded while the
@@ -721,9 +733,17 @@ __global__ __launch_bounds__(kThreads) void k_sort_pass(SortArgs a, int pass) {
   L.gstart[tid] = block_excl_scan(gtotal, L.tmp);  // contains the barrier publishing s_tile
   const uint32_t tile = s_tile;
   if (tile != blockIdx.x) load_tile(tile);
-  if (pass == 0 && tile == 0 && a.skew_out != nullptr)
-    record_max(large_bucket(mine[static_cast<size_t>(a.passes - 1) * kRadix + tid]), a.skew_out,
-               L.tmp);
+  // The largest top digit, for the choice of the next sorts: without the batch's
+  // padding, which the top-digit sort does not sort either.
+  if (pass == 0 && tile == 0 && a.skew_out != nullptr) {
+    const int top = a.passes - 1;
+    uint32_t c = mine[static_cast<size_t>(top) * kRadix + tid];
+    if (a.src.n < b) {
+      const uint32_t kv_last = src_kv(a.src, a.src.keys[a.src.n - 1], a.src.n - 1);
+      if (((kv_last >> (a.lo_bit + kRadixBits * top)) & (kRadix - 1)) == tid) c -= b - a.src.n;
+    }
+    record_max(large_bucket(c), a.skew_out, L.tmp);
+  }
   uint32_t* st = m.status + static_cast<size_t>(pass) * m.num_sort_tiles * kRadix;
   sort_tile_pass(kv, val, tile, b, a.lo_bit + kRadixBits * pass, st, o_kv, o_val,
                  (pass == a.passes - 1) ? a.out_fence : nullptr, false, &m.err[1], L);
@@ -789,18 +809,6 @@ struct LsdSrc {
   const uint32_t* kv;
   const uint32_t* val;
 };
-
-// Where element e < b of the batch, as the sort sees it (read back to front and
-// padded in front), stands in the caller's arrays.
-__device__ __forceinline__ uint32_t src_index(const BatchSrc& s, uint32_t e) {
-  const uint32_t x = s.b - 1 - e;
-  return x < s.n - 1 ? x : s.n - 1;
-}
-__device__ __forceinline__ uint32_t src_kv(const BatchSrc& s, uint32_t raw, uint32_t i) {
-  if (s.mode == kEncoded) return raw;
-  const uint32_t st = s.mode == kMixed ? (s.is_delete[i] ? 0u : 1u) : (s.mode == kDelete ? 0u : 1u);
-  return (raw << 1) | st;
-}
 
 __global__ __launch_bounds__(kLsdThreads) void k_lsd_up(SortArgs a, LsdSrc in, int shift,
                                                         uint32_t tiles_per_group,
