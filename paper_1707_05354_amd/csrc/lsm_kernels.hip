@@ -1859,6 +1859,9 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
     return p;
   };
   // Writes the bucket's padding; o: the output position of its first element.
+  // One work-group writes all of a batch's copies, four a store (the outputs are
+  // 16-byte aligned): 32 partly filled batches of 2^19 take 1719 us, 4081 with one
+  // a store (3550 by digit passes); 255 of 2^16 3436, 4566.
   auto write_pads = [&](uint32_t* kv, uint32_t* val, uint32_t* fence, uint64_t len, uint64_t o) {
     if (!kPads || here == 0) return;
 #pragma unroll
@@ -1870,11 +1873,21 @@ __device__ void bucket_sort(const SortArgs& a, int lo_bit, int passes, uint32_t 
         p += ((here >> y) & 1u) != 0 && L.pad_at[y] < L.pad_at[q] ? pad_n[y] : 0u;
       const uint64_t e = p + pad_n[q] < len ? p + pad_n[q] : len;
       const uint32_t v = a.grp_pad[q][1];
-      for (uint64_t x = p + tid; x < e; x += kThreads) {
-        kv[x] = pad_kv[q];
-        val[x] = v;
-        put_fence(fence, len, x, pad_kv[q]);
+      const uint64_t p4 = min((p + 3) & ~uint64_t(3), e), e4 = max(e & ~uint64_t(3), p4);
+      // Up to three copies before the first aligned place and after the last.
+      const uint64_t edge = tid < p4 - p ? p + tid : e4 + (tid - (p4 - p));
+      if (edge < (tid < p4 - p ? p4 : e)) {
+        kv[edge] = pad_kv[q];
+        val[edge] = v;
       }
+      const uint4 k4 = make_uint4(pad_kv[q], pad_kv[q], pad_kv[q], pad_kv[q]), v4 = make_uint4(v, v, v, v);
+      for (uint64_t x = p4 + 4 * tid; x < e4; x += 4 * kThreads) {
+        *reinterpret_cast<uint4*>(kv + x) = k4;
+        *reinterpret_cast<uint4*>(val + x) = v4;
+      }
+      if (fence != nullptr)
+        for (uint64_t x = ((p + 31) & ~uint64_t(31)) + 32 * tid; x < e; x += 32 * kThreads)
+          put_fence(fence, len, x, pad_kv[q]);
     }
   };
   if (kPads && tid < kMaxGroup) L.pad_at[tid] = 0u;
