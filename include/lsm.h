@@ -304,7 +304,9 @@ LSM_API lsm_status_t lsm_range(lsm_t h, const uint32_t* d_lo, const uint32_t* d_
  *   d_keys, d_vals : n keys and values (device), read only.
  * n == 0 is a no-op.  Needs scratch (the sort's ping-pong and counts for the
  * largest level built, two merge buffers when old levels are taken over),
- * which the handle keeps for later calls and shares with lsm_cleanup;
+ * which the handle keeps for later calls and shares with lsm_cleanup, up to
+ * 2 GiB (larger scratch is freed before the call returns); it is given back when
+ * an allocation of any handle on the GPU finds no memory, and on lsm_destroy;
  * synchronises the stream.  LSM_EINVAL, LSM_EKEY (checked mode; nothing changed),
  * LSM_ENOMEM (nothing changed), LSM_ECAPACITY (n >= 2^32 or a level above
  * 2^31 elements), LSM_EHIP.
@@ -340,9 +342,8 @@ LSM_API lsm_status_t lsm_predecessor(lsm_t h, const uint32_t* d_q, uint32_t nq,
  * smaller levels.  Every query answer is unchanged; later batches insert on
  * top of r' as usual.
  *   h_valid : HOST pointer (may be NULL); receives the number of valid pairs.
- * Needs scratch of up to 2 r b (key, value) pairs, which the handle keeps for
- * later calls and shares with lsm_bulk_insert (it gives it back when another
- * of its allocations finds no memory); synchronises the stream.  LSM_EINVAL, LSM_ENOMEM
+ * Needs scratch of up to 2 r b (key, value) pairs, kept and given back as that of
+ * lsm_bulk_insert; synchronises the stream.  LSM_EINVAL, LSM_ENOMEM
  * (nothing changed), LSM_ECAPACITY (r b >= 2^32), LSM_EHIP.
  */
 LSM_API lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid);

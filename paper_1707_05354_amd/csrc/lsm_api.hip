@@ -12,6 +12,7 @@
 // dictionary as it was.
 #include <algorithm>
 #include <chrono>
+#include <mutex>
 #include <new>
 #include <string.h>
 #include <vector>
@@ -37,6 +38,10 @@ static_assert(kSpanUpdate >= kNumKernelKinds, "span kinds overlap kernel kinds")
 // same 1024 batches took 22.3 ms of device time against 16.4 ms when the
 // host stayed a few launches ahead.
 constexpr int kDefaultInflight = 4;
+// Most scratch that a handle keeps between bulk insertions and cleanups (bulk
+// insertion of 2^25 pairs into a filled dictionary takes 1.2 GiB): other users of
+// the GPU cannot ask for it back.
+constexpr size_t kKeptWork = size_t(2) << 30;
 // A pacing wait gives up after this long (the device has stopped writing
 // its progress, e.g. after a fault; the call then goes ahead unpaced).
 constexpr int kPaceLimitMs = 500;
@@ -118,13 +123,15 @@ struct lsm_s {
   FixedScratch fixed = {nullptr, nullptr};
 
   // Scratch of lsm_bulk_insert and lsm_cleanup, grown to the largest such call
-  // and kept for the next one: allocating and freeing it took 1 to 13 ms a
-  // call (hipFree waits for the device and hands the memory back to the
-  // driver), more than the kernels of either call on 2^24 pairs.  Given back
-  // when another allocation of the handle finds no memory.
+  // and kept for the next one, up to kKeptWork: allocating and freeing it took 1
+  // to 13 ms a call (hipFree waits for the device and hands the memory back to
+  // the driver), more than the kernels of either call on 2^24 pairs.  Given back
+  // when an allocation of any handle on the GPU finds no memory.  Guarded by
+  // g_work_mu, as the list of the handles.
   void* work = nullptr;
   size_t work_bytes = 0;
   bool work_busy = false;
+  lsm_s* next_handle = nullptr;
 
   uint64_t* h_pinned = nullptr;  // read-backs (range total, key check)
   // Largest top-digit bucket of the most recent sort, written by the sort
@@ -197,26 +204,43 @@ bool alloc_allowed(lsm_t h) {
   return true;
 }
 
-lsm_status_t dev_alloc(lsm_t h, void** p, size_t bytes, bool counted = true) {
-  *p = nullptr;
-  if (counted && !alloc_allowed(h)) return LSM_ENOMEM;
-  if (bytes == 0) bytes = 4;
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess && h->work != nullptr && !h->work_busy) {
-    // The kept scratch makes room (both calls that use it end with a
-    // synchronisation, so no work on the device still needs it).
-    (void)hipGetLastError();
-    (void)hipFree(h->work);
-    h->device_bytes -= h->work_bytes;
-    h->work = nullptr;
-    h->work_bytes = 0;
-    e = hipMalloc(p, bytes);
+std::mutex g_work_mu;
+lsm_s* g_handles = nullptr;  // every handle of the process
+
+// Gives back the kept scratch of every handle on the GPU that is not in a call
+// that uses it (both calls end with a synchronisation, so no work on the device
+// needs it either).  Whether any was given back.
+bool release_idle_work(int device) {
+  std::lock_guard<std::mutex> lock(g_work_mu);
+  bool any = false;
+  for (lsm_s* x = g_handles; x != nullptr; x = x->next_handle) {
+    if (x->device != device || x->work == nullptr || x->work_busy) continue;
+    (void)hipFree(x->work);
+    x->work = nullptr;
+    x->work_bytes = 0;
+    any = true;
   }
+  return any;
+}
+
+// hipMalloc, with the kept scratch given back when memory runs out.
+bool raw_alloc(int device, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
-    *p = nullptr;
-    return LSM_ENOMEM;
+    if (release_idle_work(device)) e = hipMalloc(p, bytes);
   }
+  if (e == hipSuccess) return true;
+  (void)hipGetLastError();
+  *p = nullptr;
+  return false;
+}
+
+lsm_status_t dev_alloc(lsm_t h, void** p, size_t bytes) {
+  *p = nullptr;
+  if (!alloc_allowed(h)) return LSM_ENOMEM;
+  if (bytes == 0) bytes = 4;
+  if (!raw_alloc(h->device, p, bytes)) return LSM_ENOMEM;
   h->device_bytes += bytes;
   return LSM_OK;
 }
@@ -230,7 +254,9 @@ void dev_free(lsm_t h, void* p, size_t bytes) {
 
 // The kept scratch, cut into 256-byte aligned parts for one call: add() every
 // part, claim() once (it allocates only when the scratch has to grow), then
-// part() gives the addresses.  Free for the next call when the object goes.
+// part() gives the addresses.  Free for the next call, or given back when it is
+// larger than what is kept, when the object goes.  claim() comes after the call's
+// other allocations, which may need memory that the kept scratch holds.
 struct WorkArea {
   lsm_t h;
   size_t at[10] = {};
@@ -239,7 +265,14 @@ struct WorkArea {
   bool claimed = false;
   explicit WorkArea(lsm_t handle) : h(handle) {}
   ~WorkArea() {
-    if (claimed) h->work_busy = false;
+    if (!claimed) return;
+    std::lock_guard<std::mutex> lock(g_work_mu);
+    h->work_busy = false;
+    if (h->work_bytes > kKeptWork) {
+      (void)hipFree(h->work);
+      h->work = nullptr;
+      h->work_bytes = 0;
+    }
   }
   int add(size_t bytes) {
     at[n] = total;
@@ -251,14 +284,21 @@ struct WorkArea {
   lsm_status_t claim() {
     for (int i = 0; i < n; ++i)
       if (!alloc_allowed(h)) return LSM_ENOMEM;
-    if (h->work_bytes < total) {
-      dev_free(h, h->work, h->work_bytes);
+    void* grow = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(g_work_mu);
+      if (h->work_bytes >= total) {
+        h->work_busy = claimed = true;
+        return LSM_OK;
+      }
+      if (h->work != nullptr) (void)hipFree(h->work);
       h->work = nullptr;
       h->work_bytes = 0;
-      const lsm_status_t s = dev_alloc(h, &h->work, total, false);
-      if (s != LSM_OK) return s;
-      h->work_bytes = total;
     }
+    if (!raw_alloc(h->device, &grow, total)) return LSM_ENOMEM;
+    std::lock_guard<std::mutex> lock(g_work_mu);
+    h->work = grow;
+    h->work_bytes = total;
     h->work_busy = claimed = true;
     return LSM_OK;
   }
@@ -404,7 +444,18 @@ void release_all(lsm_t h) {
     dev_free(h, h->q_status, scan_status_words(static_cast<uint32_t>(h->q_cap)) * sizeof(uint64_t));
   }
   dev_free(h, h->q_bounds, h->q_bwords * sizeof(uint32_t));
-  dev_free(h, h->work, h->work_bytes);
+  {
+    std::lock_guard<std::mutex> lock(g_work_mu);
+    for (lsm_s** x = &g_handles; *x != nullptr; x = &(*x)->next_handle) {
+      if (*x == h) {
+        *x = h->next_handle;
+        break;
+      }
+    }
+    if (h->work != nullptr) (void)hipFree(h->work);
+    h->work = nullptr;
+    h->work_bytes = 0;
+  }
   if (h->h_pinned) (void)hipHostFree(h->h_pinned);
   if (h->skew_host) (void)hipHostFree(h->skew_host);
   if (h->progress_host) (void)hipHostFree(h->progress_host);
@@ -997,6 +1048,11 @@ lsm_status_t lsm_create(lsm_t* out, uint32_t b, uint32_t flags, void* stream) {
     delete h;
     return LSM_EHIP;
   }
+  {
+    std::lock_guard<std::mutex> lock(g_work_mu);
+    h->next_handle = g_handles;
+    g_handles = h;
+  }
   const size_t bb = static_cast<size_t>(b) * sizeof(uint32_t);
   {
     const uint32_t tiles = (b + kSortTile - 1) / kSortTile;
@@ -1238,8 +1294,8 @@ lsm_status_t lsm_bulk_insert(lsm_t h, const uint32_t* d_keys, const uint32_t* d_
       if (merges) mg[q][c] = wk.add(max_level * sizeof(uint32_t));
     }
   const int meta_part = wk.add(meta_bytes);
-  s = wk.claim();
   for (int q = 0; q < np && s == LSM_OK; ++q) s = ensure_level(h, plan[q].level);
+  if (s == LSM_OK) s = wk.claim();
   if (s == LSM_OK) s = settle(h);  // allocates nothing now
   if (s != LSM_OK) return s;
   if (h->r != r0) return LSM_EHIP;
@@ -1354,8 +1410,8 @@ lsm_status_t lsm_cleanup(lsm_t h, uint64_t* h_valid) {
   for (int q = 0; q < nbuf; ++q)
     for (int c = 0; c < 2; ++c) part[q][c] = wk.add(bytes);
   const int off_part = wk.add((tiles + 1ull) * sizeof(uint64_t));
-  s = wk.claim();
-  if (s == LSM_OK) s = ensure_query_scratch(h, tiles);
+  s = ensure_query_scratch(h, tiles);
+  if (s == LSM_OK) s = wk.claim();
   if (s == LSM_OK) s = settle(h);  // allocates nothing now
   if (s == LSM_OK && h->r != r_all) s = LSM_EHIP;
   if (s != LSM_OK) return s;
@@ -1879,7 +1935,10 @@ lsm_status_t lsm_get_stats(lsm_t h, lsm_stats_t* out) {
   out->merged_elems_last = h->merged_last;
   out->merged_elems_total = h->merged_total;
   out->sorted_elems_total = h->sorted_total;
-  out->device_bytes = h->device_bytes;
+  {
+    std::lock_guard<std::mutex> lock(g_work_mu);
+    out->device_bytes = h->device_bytes + h->work_bytes;
+  }
   out->sorts_top_digit = h->sorts_by_path[kSortMsd];
   out->sorts_digit_passes = h->sorts_by_path[kSortLsd];
   return LSM_OK;

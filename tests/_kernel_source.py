@@ -53,10 +53,10 @@ def run(tmp_path, program, patterns, sanitize):
                           env=dict(os.environ, TSAN_OPTIONS="halt_on_error=1"))
 
 
-def run_host_code(tmp_path, program, wrap=None):
+def run_host_code(tmp_path, program, wrap=()):
     """Builds and runs a program over the library's host code (csrc/lsm_api.hip)
-    and the stand-in runtime and launchers of tests/host_sanitize/.  wrap: a
-    launcher whose calls go to the program's __wrap_ function."""
+    and the stand-in runtime and launchers of tests/host_sanitize/.  wrap: the
+    functions whose calls go to the program's __wrap_ functions."""
     from test_host_sanitize import extract_layout
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
@@ -68,8 +68,7 @@ def run_host_code(tmp_path, program, wrap=None):
            "-fno-sanitize-recover=all", "-I", san, "-I", str(tmp_path), "-I", CSRC,
            "-I", os.path.join(ROOT, "include"), "-x", "c++", os.path.join(CSRC, "lsm_api.hip"),
            "-x", "none", os.path.join(san, "stand_in.cpp"), program, "-o", exe]
-    build = subprocess.run(cmd + (["-Wl,--wrap=" + wrap] if wrap else []),
-                           capture_output=True, text=True, timeout=600)
+    build = subprocess.run(cmd + ["-Wl,--wrap=" + w for w in wrap], capture_output=True, text=True, timeout=600)
     if build.returncode != 0 and "sanitize" in build.stderr and "cannot find" in build.stderr:
         pytest.skip("sanitizer runtime not installed: " + build.stderr.strip()[:200])
     assert build.returncode == 0, build.stderr[-4000:]
