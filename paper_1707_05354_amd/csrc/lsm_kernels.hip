@@ -3606,7 +3606,7 @@ constexpr uint32_t kCleanTile = kThreads * kCleanItems;
 __device__ __forceinline__ void clean_load(const uint32_t* list, uint32_t n, uint32_t e0,
                                            uint32_t (&x)[kCleanItems]) {
   static_assert(kCleanItems == 8, "two 16-byte loads (the lists are 256-byte aligned)");
-  if (e0 + 8u <= n) {
+  if (e0 < n && n - e0 >= 8u) {  // (e0 + 8 may be 2^32)
     const uint4 a = *reinterpret_cast<const uint4*>(list + e0);
     const uint4 b = *reinterpret_cast<const uint4*>(list + e0 + 4);
     x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w;
