@@ -19,8 +19,6 @@ constexpr int kRadix = 1 << kRadixBits;
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kThreads * kSortItems;
 constexpr int kMaxPasses = 4;
-// The histogram kernel uses at most this many work-groups (tile-strided).
-constexpr int kMaxHistBlocks = 512;
 // Batches of at most kMsdMaxTiles tiles use the two-kernel top-digit sort:
 // each tile grouped in place by its top kTopBits bits, then one work-group
 // per top-digit bucket gathers its group from every tile.  Buckets (and

@@ -26,7 +26,8 @@
 //   k_count / k_range_emit : per-query bounds in every occupied level and a
 //       merge of the per-level candidate runs in level order, keeping the
 //       first element of each key run when it is a regular element
-//       (sec. III-E, IV-C, IV-D).  k_range_emit_one : the emission with one
+//       (sec. III-E, IV-C, IV-D), eight lanes a query or, where every query of
+//       a wave has few candidates, one.  k_range_emit_one : the emission with one
 //       occupied level, a wave copying one query's candidates at a time.
 //   k_scan : single-pass exclusive scan with decoupled look-back for the
 //       range output offsets (stage 2 of sec. IV-C).
@@ -640,8 +641,9 @@ __device__ void sort_tile_pass(const uint32_t (&kv)[kSortItems], const uint32_t 
   __syncthreads();
 }
 
-// Digit histograms of every pass in one read of the batch, accumulated into
-// hist[parity] (LDS first, then one global atomic per non-zero bucket).
+// Digit histograms of every pass in one read of the batch, a tile a work-group,
+// accumulated into hist[parity] (LDS first, then one global atomic per non-zero
+// bucket).
 // Also clears hist[parity ^ 1] for the next sort, and this sort's look-back
 // words and tile counters.
 __global__ __launch_bounds__(kThreads) void k_sort_hist(SortArgs a) {
@@ -658,17 +660,14 @@ __global__ __launch_bounds__(kThreads) void k_sort_hist(SortArgs a) {
   for (uint32_t i = tid; i < static_cast<uint32_t>(kMaxPasses * kRadix); i += kThreads) s_h[i] = 0u;
   __syncthreads();
 
-  for (uint32_t t = blockIdx.x; t < m.num_sort_tiles; t += gridDim.x) {
-    const uint32_t tb = t * kSortTile;
-    uint32_t kv[kSortItems], key[kSortItems], val[kSortItems];
-    bool valid[kSortItems];
-    tile_items<kSortItems>(a.src, tb, wave, lane, kv, val, key, valid);  // all loads, then count
+  uint32_t kv[kSortItems], key[kSortItems], val[kSortItems];
+  bool valid[kSortItems];
+  tile_items<kSortItems>(a.src, blockIdx.x * kSortTile, wave, lane, kv, val, key, valid);
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-      if (!valid[i]) continue;
-      for (int p = 0; p < a.passes; ++p)
-        atomicAdd(&s_h[p * kRadix + ((kv[i] >> (a.lo_bit + kRadixBits * p)) & (kRadix - 1))], 1u);
-    }
+  for (int i = 0; i < kSortItems; ++i) {
+    if (!valid[i]) continue;
+    for (int p = 0; p < a.passes; ++p)
+      atomicAdd(&s_h[p * kRadix + ((kv[i] >> (a.lo_bit + kRadixBits * p)) & (kRadix - 1))], 1u);
   }
   __syncthreads();
   uint32_t* mine = m.hist + static_cast<size_t>(m.parity) * kMaxPasses * kRadix;
@@ -3930,8 +3929,7 @@ hipError_t launch_sort(const SortArgs& a, hipStream_t stream, const KTimer* time
     *launched = 1 + a.passes;
     return hipSuccess;
   }
-  const uint32_t hist_grid = tiles < static_cast<uint32_t>(kMaxHistBlocks) ? tiles : kMaxHistBlocks;
-  hipError_t e = launch(k_sort_hist, hist_grid, kThreads, stream, timers ? &timers[0] : nullptr, a);
+  hipError_t e = launch(k_sort_hist, tiles, kThreads, stream, timers ? &timers[0] : nullptr, a);
   if (e != hipSuccess) return e;
   *launched = 1;
   for (int p = 0; p < a.passes; ++p) {
@@ -4018,11 +4016,13 @@ hipError_t launch_fill_runs(uint32_t* a_kv, uint32_t* a_val, uint32_t* b_kv, uin
 // work-group (k_lookup_few and the like) and the tops, whose loading would be
 // part of every query's latency, are not used.  The two ways cross between
 // 2^17 and 2^18 queries: lookups on ten levels take 60 us dealt and 69 with
-// tops at 2^17, 111 and 96 at 2^18; counts 80 and 118, 143 and 163.  Order
+// tops at 2^17, 111 and 96 at 2^18; counts 80 and 118, 143 and 163 (where lanes
+// count alone, on small dictionaries, the lines are closer: one key on three levels
+// of 0.7 M 28 and 20 at 2^17, but 16 keys 44 and 59).  Order
 // queries, whose first wave works on alone, cross at half of that: successors
 // on seven levels 45 and 60 at 2^16, 73 and 71 at 2^17.  Above, the grid is as large as keeps the
 // loading of the tops small beside the queries (with one level 2^22 lookups
-// take 212 us in 4096 work-groups, 222 in 1280).  Where nothing is dealt (one
+// take 212 us in 5120 work-groups, 222 in 1280).  Where nothing is dealt (one
 // level counted, emission that searches) tops pay from half of kFewQueries on:
 // 2^17 counts on one level take 21.6 us with them, 23.1 without.
 constexpr uint32_t kFewQueries = 1u << 17;

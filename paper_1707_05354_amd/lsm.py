@@ -46,8 +46,13 @@ KERNEL_NAMES = ("k_sort_hist", "k_sort_pass", "k_merge", "k_lookup", "k_count", 
                 "k_local_sort", "k_sort_step")
 # rocprofv3 kernel names behind each profiler kind that covers several kernels.
 KERNEL_TRACE_NAMES = {"k_lookup": ("k_lookup", "k_lookup_few"),
-                      "k_count": ("k_count<false, false>", "k_count<true, false>", "k_count<true, true>",
-                                  "k_count_few"),
+                      "k_count": ("k_count<false, false, 0>", "k_count<true, false, 0>", "k_count<true, true, 0>",
+                                  "k_count<true, true, 3>", "k_count<true, true, 6>",
+                                  "k_count<true, true, 10>", "k_count_few"),
+                      "k_range_emit": ("k_range_emit_one<false, 4, false>", "k_range_emit_one<false, 4, true>",
+                                       "k_range_emit_one<true, 4, true>", "k_range_emit<false, false, 3>",
+                                       "k_range_emit<false, false, 6>", "k_range_emit<false, false, 10>",
+                                       "k_range_emit<false, true, 0>", "k_range_emit<true, true, 0>"),
                       "k_order": ("k_successor<false>", "k_successor<true>", "k_predecessor<false>",
                                   "k_predecessor<true>"),
                       "k_clean": ("k_clean_count", "k_clean_scatter", "k_clean_pad"),
