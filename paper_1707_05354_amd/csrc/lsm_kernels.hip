@@ -2942,15 +2942,19 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_count_few(QLevels lv, const 
   }
 }
 
-// Queries of few candidates over at most kN levels: a lane walks its own query,
-// a step for every key, the levels' next elements in registers.  A level has an
-// element while its cursor is below its length: every 32-bit word is the key
-// variable of some element (all ones that of key 2^31 - 1), so no word can stand
-// for none.  (Octets need a round for each of a wave's queries, however few
-// candidates it has.)
+// Queries of few candidates over at most kN levels: a lane walks its own query, the
+// levels' next elements in registers.  A level has an element while its cursor is
+// below its length: every 32-bit word is the key variable of some element (all ones
+// that of key 2^31 - 1), so no word can stand for none.  (Octets need a round for
+// each of a wave's queries, however few candidates it has.)
+// kRuns: a step passes over a key's whole run in a level, else over one element,
+// so that older elements of the key take steps of their own.  Whole runs cost the
+// steps 5 to 10 % where the levels lie in the L2s, and single elements the ranges
+// of four keys on larger levels 4 %: a key and its tombstone in one level are
+// common, and every further step of one lane is one of the whole wave.
 constexpr int kNarrowLevels = 10;
 constexpr uint32_t kNarrowSteps = 40;
-template <int kN>
+template <int kN, bool kRuns>
 struct NarrowWalk {
   uint32_t c[kN], x[kN];
   uint32_t key, last;  // the step's key, and that of the step before
@@ -2985,14 +2989,20 @@ struct NarrowWalk {
   }
   // Whether `elem` is a live pair: a regular element and not an older one of the
   // key of the step before.
-  __device__ __forceinline__ bool live() const { return key != last && (elem & 1u) != 0u; }
-  // Past one element of the key in every level that has it.
+  __device__ __forceinline__ bool live() const {
+    return (kRuns || key != last) && (elem & 1u) != 0u;
+  }
+  // Past the key's run, or one element of it, in every level that has it.
   __device__ __forceinline__ void pass(const QLevels& lv) {
 #pragma unroll
     for (int l = 0; l < kN; ++l) {
       if (c[l] < lv.v[l].len && (x[l] >> 1) == key) {
         ++c[l];
         x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
+        if (kRuns && c[l] < lv.v[l].len && (x[l] >> 1) == key) {
+          c[l] = skip_run(lv.v[l].kv, c[l], lv.v[l].len, key);
+          x[l] = c[l] < lv.v[l].len ? lv.v[l].kv[c[l]] : 0u;
+        }
       }
     }
   }
@@ -3009,7 +3019,7 @@ __device__ __forceinline__ bool count_narrow(const QLevels& lv, const uint32_t* 
   const bool reaches = c < last.len && last.len - c > far;
   const uint32_t z = reaches ? last.kv[c + far] : 0u;
   if (ballot(reaches && z <= h) != 0) return false;
-  NarrowWalk<kN> w;
+  NarrowWalk<kN, false> w;
   w.start(lv, cur, true);
   uint32_t n = 0;
   bool more = true;
@@ -3025,12 +3035,12 @@ __device__ __forceinline__ bool count_narrow(const QLevels& lv, const uint32_t* 
 // Writes pairs [o, z) of the lane's query from the cursors in cur; gives up after
 // kNarrowSteps steps (many deleted keys or long runs).  Returns whether every lane
 // of the wave has written all its pairs; writing them again is harmless.
-template <int kN>
+template <int kN, bool kRuns>
 __device__ __forceinline__ bool emit_narrow(const QLevels& lv, const uint32_t* cur, uint32_t k2,
                                             uint64_t o, uint64_t z, uint32_t* out_keys,
                                             uint32_t* out_vals) {
   const uint32_t h = ((k2 < kMaxKey ? k2 : kMaxKey) << 1) | 1u;
-  NarrowWalk<kN> w;
+  NarrowWalk<kN, kRuns> w;
   w.start(lv, cur, o < z);
   for (uint32_t i = 0; i < kNarrowSteps && ballot(o < z) != 0; ++i) {
     if (!w.next(lv, h)) break;  // no query, or only after a timed-out scan
@@ -3125,7 +3135,7 @@ __global__ __launch_bounds__(kQueryThreads) void k_count(QLevels lv,
 // most narrow_max pairs emit lane by lane.  (Without the bound of five waves a
 // SIMD the lane walk takes registers from the octets': 16 pairs a query on six
 // levels 345 us with it, 389 without.)
-template <bool kTop, bool kSearch, int kN>
+template <bool kTop, bool kSearch, int kN, bool kRuns>
 __global__ __launch_bounds__(kQueryThreads, kSearch ? 1 : 5) void k_range_emit(QLevels lv,
                                                               const uint32_t* lo,
                                                               const uint32_t* hi, uint32_t nq,
@@ -3168,7 +3178,7 @@ __global__ __launch_bounds__(kQueryThreads, kSearch ? 1 : 5) void k_range_emit(Q
     bool narrow = false;
     if constexpr (kN != 0)
       narrow = per == 8 && ballot(z - o > narrow_max) == 0 &&
-               emit_narrow<kN>(lv, w.cur + lane, k2, o, z, out_keys, out_vals);
+               emit_narrow<kN, kRuns>(lv, w.cur + lane, k2, o, z, out_keys, out_vals);
     if (narrow) {
       wave_sync();
       continue;
@@ -4056,14 +4066,15 @@ static uint32_t queries_per_octet(uint32_t nq) {
 // knows its pairs and keeps to eight (2^20 ranges of one key on three levels of
 // 45 M 380 and 281), up to six levels.
 struct NarrowRule {
-  bool count;
+  bool count, runs;
   uint32_t far, pairs;
 };
 static NarrowRule narrow_rule(const LevelSet& lv) {
   uint64_t n = 0;
   for (int l = 0; l < lv.count; ++l) n += lv.len[l];
-  if (lv.count > kNarrowLevels) return {false, 0, 0};
-  return n <= (1u << 21) ? NarrowRule{true, 11, 12} : NarrowRule{false, 0, lv.count <= 6 ? 8u : 0u};
+  if (lv.count > kNarrowLevels) return {false, false, 0, 0};
+  return n <= (1u << 21) ? NarrowRule{true, false, 11, 12}
+                         : NarrowRule{false, true, 0, lv.count <= 6 ? 8u : 0u};
 }
 // LDS words of the several-level walk of one work-group.
 static unsigned walk_lds_words(const QLevels& q, bool emit) {
@@ -4184,10 +4195,13 @@ hipError_t launch_range_emit(const LevelSet& lv, const uint32_t* lo, const uint3
                       grid, kQueryThreads, ql.words * 4u, stream, t, ql, lo, hi, nq, offsets,
                       bounds, out_keys, out_vals, cap);
   const NarrowRule nr = narrow_rule(lv);
-  auto k = bounds == nullptr ? (top ? k_range_emit<true, true, 0> : k_range_emit<false, true, 0>)
-           : lv.count <= 3   ? k_range_emit<false, false, 3>
-           : lv.count <= 6   ? k_range_emit<false, false, 6>
-                             : k_range_emit<false, false, kNarrowLevels>;
+  auto k = bounds == nullptr ? (top ? k_range_emit<true, true, 0, false>
+                                    : k_range_emit<false, true, 0, false>)
+           : lv.count <= 3   ? (nr.runs ? k_range_emit<false, false, 3, true>
+                                        : k_range_emit<false, false, 3, false>)
+           : lv.count <= 6   ? (nr.runs ? k_range_emit<false, false, 6, true>
+                                        : k_range_emit<false, false, 6, false>)
+                             : k_range_emit<false, false, kNarrowLevels, false>;
   const unsigned lds = (ql.words + walk_lds_words(ql, true)) * 4u;
   const uint32_t per = queries_per_octet(nq);
   return launch_lds(k, grid_for(nq, kQueryThreads / 8 * per), kQueryThreads, lds, stream, t, ql,

@@ -50,9 +50,10 @@ KERNEL_TRACE_NAMES = {"k_lookup": ("k_lookup", "k_lookup_few"),
                                   "k_count<true, true, 3>", "k_count<true, true, 6>",
                                   "k_count<true, true, 10>", "k_count_few"),
                       "k_range_emit": ("k_range_emit_one<false, 4, false>", "k_range_emit_one<false, 4, true>",
-                                       "k_range_emit_one<true, 4, true>", "k_range_emit<false, false, 3>",
-                                       "k_range_emit<false, false, 6>", "k_range_emit<false, false, 10>",
-                                       "k_range_emit<false, true, 0>", "k_range_emit<true, true, 0>"),
+                                       "k_range_emit_one<true, 4, true>") + tuple(
+                          "k_range_emit<false, false, %s>" % x
+                          for x in ("3, false", "3, true", "6, false", "6, true", "10, false")) + (
+                          "k_range_emit<false, true, 0, false>", "k_range_emit<true, true, 0, false>"),
                       "k_order": ("k_successor<false>", "k_successor<true>", "k_predecessor<false>",
                                   "k_predecessor<true>"),
                       "k_clean": ("k_clean_count", "k_clean_scatter", "k_clean_pad"),

@@ -71,8 +71,9 @@ int main() {
       return 1;
     }
     if (count <= 6 && count > 3
-            ? emit_narrow<6>(lv, cur.data(), k2, 1, 1 + want.size(), keys.data(), vals.data())
-            : emit_narrow<kNarrowLevels>(lv, cur.data(), k2, 1, 1 + want.size(), keys.data(), vals.data())) {
+            ? emit_narrow<6, true>(lv, cur.data(), k2, 1, 1 + want.size(), keys.data(), vals.data())
+            : emit_narrow<kNarrowLevels, false>(lv, cur.data(), k2, 1, 1 + want.size(), keys.data(),
+                                                vals.data())) {
       ++checked;
       for (size_t i = 0; i < want.size(); ++i) {
         if (keys[1 + i] != want[i].first || vals[1 + i] != want[i].second) {
